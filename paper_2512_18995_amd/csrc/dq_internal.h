@@ -248,15 +248,17 @@ inline int zdiag_blocks(int n) {
 }
 // expectations; terms dt0..dt1 (group 0, X-free) go through the diagonal
 // kernel into dpart ([batch][blocks][nobs] doubles) when dt0 < dt1
-// marginal probabilities (kernels.hip): measured wires' physical bits in
-// wire order (pb) and ascending (asc)
+// marginal probabilities (kernels.hip): the k measured physical bits, those
+// inside a row of 2^lb amplitudes (lbit, kl of them) and those above (hbit,
+// kh, ascending), each with its bit of the outcome index (lout, hout)
 constexpr int PROB_MAXW = 12;
 struct ProbArgs {
-    int32_t n, k;
-    int32_t pb[PROB_MAXW];
-    int32_t asc[PROB_MAXW];
+    int32_t n, k, lb, kl, kh;
+    int32_t lbit[PROB_MAXW], lout[PROB_MAXW];
+    int32_t hbit[PROB_MAXW], hout[PROB_MAXW];
 };
-// amplitudes one block of k_probs_part sums (256 threads x 16)
+inline int prob_row_bits(int dbl) { return dbl ? 8 : 9; }   // 4 KiB
+// the workspace holds one partial sum per this many amplitudes of an outcome
 constexpr int64_t PROB_CHUNK = 4096;
 hipError_t launch_probs(int dbl, const void *st, int64_t batch, const ProbArgs &a, double *partial, int64_t bpo,
                         double *out, hipStream_t s);

@@ -1388,71 +1388,182 @@ __global__ __launch_bounds__(256) void k_grad_final_multi(const char *ws, const 
 
 // ============================================================ launchers
 // ============================================================ measurement
-// Marginal probabilities.  Block (x, o, b) sums |psi_b[j]|^2 over chunk x of
-// the basis states whose measured bits read o: j is the chunk index r with
-// zeros inserted at the measured physical bits (ascending) and o's bits set
-// there, so consecutive threads read consecutive amplitudes whenever the
-// measured bits lie above the low ones.  One partial per block, summed in a
-// fixed order by k_probs_final.
+// Marginal probabilities in one linear read of the state.  The low LB bits
+// (512 complex64 or 256 complex128 amplitudes: 16 bytes a thread of a
+// 256-thread group) form a row of 4 KiB; the other bits are either measured
+// (block index y: with the row bits' outcome they name the marginal) or
+// walked row by row.  A thread therefore keeps one sum per amplitude of its
+// 16 bytes, whichever wires are measured, and every load is one contiguous
+// 4 KiB piece; the measured bits inside the row are sorted out once per
+// block: unmeasured lane bits by shuffles, the rest through LDS, in a fixed
+// order.  HBM-bound: ten wires of 27 qubits 436 -> 238 us (2.5 -> 4.5 TB/s;
+// before, each outcome's amplitudes were read apart, with ten zero bits
+// inserted into every index).
+template <typename T> constexpr int prob_lb() { return sizeof(T) == 4 ? 9 : 8; }
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_probs_part(const cx<T> *psi, ProbArgs a, int64_t per_outcome,
-                                                    double *partial, int64_t bpo) {
-    __shared__ double red[4];
-    const int64_t o = blockIdx.y, b = blockIdx.z;
-    const int K = 1 << a.k;
+__global__ __launch_bounds__(1024) void k_probs_part(const cx<T> *psi, ProbArgs a, int64_t rows, int64_t rpb,
+                                                     double *partial, int64_t bpo) {
+    constexpr int A = sizeof(T) == 4 ? 2 : 1, LB = prob_lb<T>(), U = 8;
+    typedef T vld __attribute__((ext_vector_type(2 * A), aligned(2 * sizeof(T))));
+    __shared__ double sh[4][256 * A];
+    const int tid = threadIdx.x & 255;
+    const int grp = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8));
+    const int64_t oh = blockIdx.y, b = blockIdx.z;
     uint64_t set = 0;
-    for (int i = 0; i < a.k; ++i)
-        if ((o >> (a.k - 1 - i)) & 1) set |= 1ull << a.pb[i];
-    const cx<T> *p = psi + (b << a.n);
-    double acc = 0.0;
-    const int64_t r0 = (int64_t)blockIdx.x * PROB_CHUNK + threadIdx.x;
-#pragma unroll 4
-    for (int t = 0; t < (int)(PROB_CHUNK / 256); ++t) {
-        const int64_t r = r0 + t * 256;
-        if (r < per_outcome) {
-            int64_t j = r;
-            for (int i = 0; i < a.k; ++i) j = insert_zero(j, a.asc[i]);
-            const cx<T> v = p[(uint64_t)j | set];
-            acc += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+    int out_hi = 0;
+    for (int i = 0; i < a.kh; ++i)
+        if ((oh >> i) & 1) {
+            set |= 1ull << a.hbit[i];
+            out_hi |= 1 << a.hout[i];
+        }
+    const cx<T> *p = psi + (b << a.n) + set + tid * A;
+    const bool active = (int64_t)tid * A < (int64_t(1) << a.n);   // registers shorter than a row
+    const int64_t r0 = (int64_t)blockIdx.x * rpb, r1 = r0 + rpb < rows ? r0 + rpb : rows;
+    double acc[A] = {};
+    if (active) {
+        for (int64_t r = r0 + grp; r < r1; r += 4 * U) {
+            vld v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int64_t j = r + 4 * u;
+                if (j >= r1) {
+                    v[u] = vld(T(0));
+                    continue;
+                }
+                for (int i = 0; i < a.kh; ++i) j = insert_zero(j, a.hbit[i] - LB);
+                v[u] = *(const vld *)(p + (j << LB));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < A; ++e) {
+                    const double x = (double)v[u][2 * e], y = (double)v[u][2 * e + 1];
+                    acc[e] += x * x + y * y;
+                }
         }
     }
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    // unmeasured bits: the two amplitudes of a thread, then the lanes
+    uint32_t low = 0;   // measured bits of the row
+    for (int i = 0; i < a.kl; ++i) low |= 1u << a.lbit[i];
+    if constexpr (A == 2)
+        if (!(low & 1)) {
+            acc[0] += acc[1];
+            acc[1] = acc[0];
+        }
+    constexpr int S = A == 2 ? 1 : 0;   // bit S + k of the row is bit k of tid
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        if (!((low >> (S + k)) & 1)) {
+#pragma unroll
+            for (int e = 0; e < A; ++e) acc[e] += __shfl_xor(acc[e], 1 << k);
+        }
+#pragma unroll
+    for (int e = 0; e < A; ++e) sh[grp][tid * A + e] = acc[e];
     __syncthreads();
-    if (threadIdx.x == 0) partial[(b * K + o) * bpo + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    const int K = 1 << a.k;
+    for (int t = threadIdx.x; t < (1 << a.kl); t += blockDim.x) {
+        int at = 0, o = out_hi;
+        for (int i = 0; i < a.kl; ++i)
+            if ((t >> i) & 1) {
+                at |= 1 << a.lbit[i];
+                o |= 1 << a.lout[i];
+            }
+        // the row's bits that are wave bits of the group: 6 and 7 of tid
+        double s = 0.0;
+        for (int g = 0; g < 4; ++g)
+            for (int w = 0; w < 4; ++w) {
+                const int wb = (w & 1) << (S + 6) | (w >> 1) << (S + 7);
+                if (wb & (int)low) continue;   // that bit is part of the outcome
+                s += sh[g][at | wb];
+            }
+        partial[(b * K + o) * bpo + blockIdx.x] = s;
+    }
 }
 
-// out[row] = sum of the row's bpo partials (row = b * 2^k + o), fixed order
-__global__ __launch_bounds__(256) void k_probs_final(const double *partial, int64_t bpo, double *out) {
-    __shared__ double red[4];
+// out[row] = sum of the row's bpo partials (row = b * 2^k + o), one wave, fixed order
+__global__ __launch_bounds__(64) void k_probs_final(const double *partial, int64_t bpo, double *out) {
     const int64_t row = blockIdx.x;
     double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < bpo; i += 256) acc += partial[row * bpo + i];
+    for (int64_t i = threadIdx.x; i < bpo; i += 64) acc += partial[row * bpo + i];
     acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) out[row] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (threadIdx.x == 0) out[row] = acc;
 }
 
-// One shot per thread: the first outcome whose running sum exceeds u.
-__global__ __launch_bounds__(256) void k_sample(const double *p, int64_t batch, int nout, const double *u, int shots,
-                                                int64_t *out) {
+// One shot per thread: the first outcome whose running sum exceeds u.  The
+// sums are the sequential float64 ones (they decide which outcome a uniform
+// near a boundary gives), so a block takes 256 shots of one distribution and
+// forms them once, 2048 outcomes at a time in LDS, on one lane; each thread
+// then finds its outcome by bisection (entries that are negative or NaN make
+// the sums non-monotone: then by scanning them in order).  Bound by that
+// chain of dependent additions: 4096 shots of 1024 outcomes 152 -> 27 us
+// (before, every shot scanned the distribution in global memory).
+constexpr int SAMPLE_CH = 2048;
+__global__ __launch_bounds__(256) void k_sample(const double *p, int nout, const double *u, int shots, int64_t *out) {
+    __shared__ double pm_[SAMPLE_CH + 16], c[SAMPLE_CH + 8];   // a chunk (zeros after its end) and its running sums
+    __shared__ double run;
+    __shared__ int last_pos, ordered;
+    const int64_t b = blockIdx.y;
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= batch * shots) return;
-    const double *q = p + (i / shots) * nout;
-    const double x = u[i];
-    double c = 0.0;
-    int64_t last = -1, res = -1;
-    for (int m = 0; m < nout; ++m) {
-        const double pm = q[m];
-        if (pm > 0.0) last = m;
-        c += pm;
-        if (x < c) {
-            res = m;
-            break;
-        }
+    const double *q = p + b * nout;
+    const bool live = i < shots;
+    const double x = live ? u[b * shots + i] : 0.0;
+    int64_t res = -1;
+    if (threadIdx.x == 0) {
+        run = 0.0;
+        last_pos = -1;
     }
-    out[i] = res >= 0 ? res : (last >= 0 ? last : 0);
+    for (int m0 = 0; m0 < nout; m0 += SAMPLE_CH) {
+        const int len = nout - m0 < SAMPLE_CH ? nout - m0 : SAMPLE_CH;
+        __syncthreads();
+        if (threadIdx.x == 0) ordered = 1;
+        __syncthreads();
+        for (int m = threadIdx.x; m < len + 16; m += 256) {
+            const double pm = m < len ? q[m0 + m] : 0.0;
+            pm_[m] = pm;
+            if (!(pm >= 0.0)) ordered = 0;
+            if (pm > 0.0) atomicMax(&last_pos, m0 + m);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            // the next eight entries are read while these are added
+            double s = run, t[8], nx[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) nx[k] = pm_[k];
+            for (int m = 0; m < len; m += 8) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) t[k] = nx[k];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) nx[k] = pm_[m + 8 + k];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) t[k] = s = s + t[k];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) c[m + k] = t[k];
+            }
+            run = s;
+        }
+        __syncthreads();
+        if (live && res < 0) {
+            if (ordered) {
+                int lo = 0, hi = len;   // first m with x < c[m], len if none
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (x < c[mid]) hi = mid;
+                    else lo = mid + 1;
+                }
+                if (lo < len) res = m0 + lo;
+            } else {
+                for (int m = 0; m < len; ++m)
+                    if (x < c[m]) {
+                        res = m0 + m;
+                        break;
+                    }
+            }
+        }
+        if (__syncthreads_and(!live || res >= 0)) break;
+    }
+    __syncthreads();
+    if (live) out[b * shots + i] = res >= 0 ? res : (last_pos >= 0 ? last_pos : 0);
 }
 
 #define DQ_LAUNCH_RET return hipGetLastError()
@@ -1766,24 +1877,28 @@ hipError_t launch_hess_accum(const double *G, int64_t K, int64_t c0, int64_t mc,
 
 hipError_t launch_probs(int dbl, const void *st, int64_t batch, const ProbArgs &a, double *partial, int64_t bpo,
                         double *out, hipStream_t s) {
-    const int64_t per_outcome = int64_t(1) << (a.n - a.k);
-    dim3 g((unsigned)bpo, (unsigned)(1u << a.k), (unsigned)batch);
+    const int64_t rows = int64_t(1) << (a.n - a.kh > a.lb ? a.n - a.kh - a.lb : 0);
+    // at most bpo blocks per outcome (the workspace), about 2048 in all: with
+    // 1024 threads each that fills the chip twice over
+    int64_t rpb = (rows + bpo - 1) / bpo;
+    while (rpb < rows && ((rows / rpb) << a.kh) * batch > 2048) rpb *= 2;
+    bpo = (rows + rpb - 1) / rpb;
+    dim3 g((unsigned)bpo, 1u << a.kh, (unsigned)batch);
+    double *part = bpo == 1 ? out : partial;   // one block per outcome: nothing to add up
     if (dbl)
-        hipLaunchKernelGGL(k_probs_part<double>, g, dim3(256), 0, s, (const C128 *)st, a, per_outcome, partial, bpo);
+        hipLaunchKernelGGL(k_probs_part<double>, g, dim3(1024), 0, s, (const C128 *)st, a, rows, rpb, part, bpo);
     else
-        hipLaunchKernelGGL(k_probs_part<float>, g, dim3(256), 0, s, (const C64 *)st, a, per_outcome, partial, bpo);
+        hipLaunchKernelGGL(k_probs_part<float>, g, dim3(1024), 0, s, (const C64 *)st, a, rows, rpb, part, bpo);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_probs_final, dim3((unsigned)(batch << a.k)), dim3(256), 0, s, (const double *)partial, bpo,
-                       out);
+    if (e != hipSuccess || bpo == 1) return e;
+    hipLaunchKernelGGL(k_probs_final, dim3((unsigned)(batch << a.k)), dim3(64), 0, s, (const double *)partial, bpo, out);
     DQ_LAUNCH_RET;
 }
 
 hipError_t launch_sample(const double *p, int64_t batch, int32_t nout, const double *u, int32_t shots, int64_t *out,
                          hipStream_t s) {
-    const int64_t total = batch * shots;
-    hipLaunchKernelGGL(k_sample, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, p, batch, nout, u, shots,
-                       out);
+    hipLaunchKernelGGL(k_sample, dim3((unsigned)((shots + 255u) / 256u), (unsigned)batch), dim3(256), 0, s, p, nout, u,
+                       shots, out);
     DQ_LAUNCH_RET;
 }
 

@@ -2158,10 +2158,19 @@ dq_status dq_probs(dq_plan plan, const void *state, int64_t batch, const int32_t
             return fail(DQ_ERR_INVALID_ARG, "wire %d outside 0..%d", wires[i], plan->n - 1);
         if ((seen >> wires[i]) & 1) return fail(DQ_ERR_INVALID_ARG, "wire %d listed twice", wires[i]);
         seen |= 1ull << wires[i];
-        a.pb[i] = plan->n - 1 - wires[i];   // wire w -> physical bit n-1-w
-        a.asc[i] = a.pb[i];
     }
-    std::sort(a.asc, a.asc + nwires);
+    a.lb = prob_row_bits(plan->dbl);
+    for (int b = 0; b < plan->n; ++b) {   // physical bits ascending; wire w -> bit n-1-w
+        const int i = (int)(std::find(wires, wires + nwires, plan->n - 1 - b) - wires);
+        if (i == nwires) continue;
+        if (b < a.lb) {
+            a.lbit[a.kl] = b;
+            a.lout[a.kl++] = nwires - 1 - i;
+        } else {
+            a.hbit[a.kh] = b;
+            a.hout[a.kh++] = nwires - 1 - i;
+        }
+    }
     if (!ws || ws_bytes < need)
         return fail(DQ_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : 0);
     ProfScope pr(*plan, DQ_PROF_OTHER, 2, state_bytes(*plan, batch), (hipStream_t)stream);
