@@ -75,72 +75,131 @@ __device__ void gate_matrix(const DGate &g, double th, const double2 *fixed, dou
     }
 }
 
-// One matrix slot of one sample: the product of its factor gates (angles
-// from the sample's params / data rows), formed in double, rounded once.
+// A one-qubit gate's matrix in registers (gate_matrix fills an array that the
+// compiler keeps in scratch memory).
+struct M2 {
+    double2 a, b, c, d;   // rows (a, b), (c, d)
+};
+__device__ __forceinline__ M2 gate2(const DGate &g, double v, const double2 *fixed) {
+    const double2 z{0.0, 0.0};
+    if (g.op == OP_UNITARY) {
+        const double2 *u = fixed + g.mat_off;
+        return M2{u[0], u[1], u[2], u[3]};
+    }
+    double s = 0.0, c = 1.0;
+    const bool phase = g.op == OP_PHASE;
+    if (phase || g.op == OP_RX || g.op == OP_RY || g.op == OP_RZ) sincos(phase ? g.scale * v : 0.5 * (g.scale * v), &s, &c);
+    const double r = 0.70710678118654752440;
+    switch (g.op) {
+    case OP_H: return M2{{r, 0}, {r, 0}, {r, 0}, {-r, 0}};
+    case OP_X: return M2{z, {1, 0}, {1, 0}, z};
+    case OP_Y: return M2{z, {0, -1}, {0, 1}, z};
+    case OP_Z: return M2{{1, 0}, z, z, {-1, 0}};
+    case OP_RX: return M2{{c, 0}, {0, -s}, {0, -s}, {c, 0}};
+    case OP_RY: return M2{{c, 0}, {-s, 0}, {s, 0}, {c, 0}};
+    case OP_RZ: return M2{{c, -s}, z, z, {c, s}};
+    default: return M2{{1, 0}, z, z, {c, s}};   // OP_PHASE
+    }
+}
+__device__ __forceinline__ double2 mul2(double2 x, double2 y, double2 u, double2 v) {   // x y + u v
+    return double2{x.x * y.x - x.y * y.y + (u.x * v.x - u.y * v.y), x.x * y.y + x.y * y.x + (u.x * v.y + u.y * v.x)};
+}
+__device__ __forceinline__ double angle_value(const DGate &g, const double *prow, const double *drow) {
+    return g.src == SRC_PARAM ? prow[g.idx] : (g.src == SRC_DATA ? drow[g.idx] : 1.0);
+}
+
+// The matrix slots of one sample, one thread a slot, formed in double from
+// the sample's params / data rows and rounded once: the product of a one-
+// qubit slot's factor gates in registers, a two-qubit gate's matrix, and the
+// fixed matrices of dense unitaries, which the whole wave copies entry by
+// entry.  Latency-bound (a few hundred slots): with the matrices in per-
+// thread arrays and one thread copying a unitary's 1024 entries, the slots
+// of a 24-qubit circuit with two 5-qubit unitaries took 196 us (the pass 1589
+// -> 1400 us; the 10-qubit complex128 step 138.8 -> 131.5 us).  Call with
+// 64-thread blocks, every lane present.
 template <typename T>
-__device__ void prepare_slot(const DGate *gates, const double2 *fixed, const DSlot &sl, const double *prow,
-                             const double *drow, cx<T> *out) {
-    const int dim = sl.dim;
-    if (dim > 4) {  // a single dense factor of 3..5 qubits
-        const DGate g = gates[sl.f[0]];
-        for (int r = 0; r < dim; ++r)
-            for (int c = 0; c < dim; ++c) {
-                double2 e = sl.dagger ? fixed[g.mat_off + c * dim + r] : fixed[g.mat_off + r * dim + c];
-                if (sl.dagger) e.y = -e.y;
-                out[r * dim + c] = cx<T>{(T)e.x, (T)e.y};
+__device__ void prepare_slots(const DGate *gates, const double2 *fixed, const DSlot *slots, int s, int nslots,
+                              const double *prow, const double *drow, cx<T> *mats) {
+    int dense = 0, dagger = 0;    // a dense unitary's dimension
+    int64_t off = 0, moff = 0;
+    if (s < nslots) {
+        const DSlot *sl = slots + s;
+        const DGate g0 = gates[sl->f[0]];
+        off = sl->off;
+        dagger = sl->dagger;
+        cx<T> *out = mats + off;
+        if (sl->dim == 2) {
+            M2 m = gate2(g0, angle_value(g0, prow, drow), fixed);
+            for (int f = 1; f < sl->nf; ++f) {   // later factors act after earlier ones
+                const DGate g = gates[sl->f[f]];
+                const M2 n = gate2(g, angle_value(g, prow, drow), fixed);
+                m = M2{mul2(n.a, m.a, n.b, m.c), mul2(n.a, m.b, n.b, m.d), mul2(n.c, m.a, n.d, m.c),
+                       mul2(n.c, m.b, n.d, m.d)};
             }
-        return;
-    }
-    double2 M[16], F[16], P[16];
-    for (int i = 0; i < dim * dim; ++i) M[i] = double2{(i % (dim + 1)) == 0 ? 1.0 : 0.0, 0.0};
-    for (int f = 0; f < sl.nf; ++f) {
-        const DGate g = gates[sl.f[f]];
-        double v = 1.0;
-        if (g.src == SRC_PARAM) v = prow[g.idx];
-        else if (g.src == SRC_DATA) v = drow[g.idx];
-        gate_matrix(g, g.scale * v, fixed, F);
-        for (int r = 0; r < dim; ++r)          // P = F * M  (F acts after M)
-            for (int c = 0; c < dim; ++c) {
-                double2 acc{0.0, 0.0};
-                for (int k = 0; k < dim; ++k) {
-                    const double2 x = F[r * dim + k], y = M[k * dim + c];
-                    acc.x += x.x * y.x - x.y * y.y;
-                    acc.y += x.x * y.y + x.y * y.x;
+            const double sg = dagger ? -1.0 : 1.0;
+            const double2 b = dagger ? m.c : m.b, c = dagger ? m.b : m.c;
+            out[0] = cx<T>{(T)m.a.x, (T)(sg * m.a.y)};
+            out[1] = cx<T>{(T)b.x, (T)(sg * b.y)};
+            out[2] = cx<T>{(T)c.x, (T)(sg * c.y)};
+            out[3] = cx<T>{(T)m.d.x, (T)(sg * m.d.y)};
+        } else if (g0.op == OP_UNITARY) {
+            dense = sl->dim;
+            moff = g0.mat_off;
+        } else {   // a two-qubit gate: diagonal, or a permutation (real, its own inverse)
+            const bool perm = g0.op == OP_CNOT || g0.op == OP_SWAP;
+            double s1 = 0.0, c1 = 1.0;
+            if (g0.op == OP_CP || g0.op == OP_RZZ) {
+                const double th = g0.scale * angle_value(g0, prow, drow);
+                sincos(g0.op == OP_CP ? th : 0.5 * th, &s1, &c1);
+                if (dagger) s1 = -s1;
+            }
+            const bool zz = g0.op == OP_RZZ;
+            const double2 d0 = zz ? double2{c1, -s1} : double2{1.0, 0.0}, d1 = zz ? double2{c1, s1} : double2{1.0, 0.0};
+            const double2 d3 = zz ? d0 : (g0.op == OP_CZ ? double2{-1.0, 0.0} : double2{c1, s1});
+            for (int r = 0; r < 4; ++r)
+                for (int c = 0; c < 4; ++c) {
+                    double2 e{0.0, 0.0};
+                    if (perm) {
+                        const int to = g0.op == OP_SWAP ? ((r & 1) << 1 | r >> 1) : (r < 2 ? r : 5 - r);
+                        e.x = c == to ? 1.0 : 0.0;
+                    } else if (r == c) {
+                        e = r == 0 ? d0 : (r == 3 ? d3 : d1);
+                    }
+                    out[r * 4 + c] = cx<T>{(T)e.x, (T)e.y};
                 }
-                P[r * dim + c] = acc;
-            }
-        for (int i = 0; i < dim * dim; ++i) M[i] = P[i];
-    }
-    for (int r = 0; r < dim; ++r)
-        for (int c = 0; c < dim; ++c) {
-            double2 e = sl.dagger ? M[c * dim + r] : M[r * dim + c];
-            if (sl.dagger) e.y = -e.y;
-            out[r * dim + c] = cx<T>{(T)e.x, (T)e.y};
         }
+    }
+    unsigned long long todo = __ballot(dense != 0);
+    while (todo) {
+        const int l = __ffsll(todo) - 1;
+        todo &= todo - 1;
+        const int dim = __shfl(dense, l), dag = __shfl(dagger, l), lg = __ffs(dim) - 1;
+        const double2 *u = fixed + __shfl((long long)moff, l);
+        cx<T> *out = mats + __shfl((long long)off, l);
+        for (int e = threadIdx.x & 63; e < dim * dim; e += 64) {
+            const double2 x = dag ? u[((e & (dim - 1)) << lg) | (e >> lg)] : u[e];
+            out[e] = cx<T>{(T)x.x, (T)(dag ? -x.y : x.y)};
+        }
+    }
 }
 
 template <typename T>
-__global__ void k_prepare(const DGate *gates, const double2 *fixed, const DSlot *slots, int nslots,
-                          const double *params, int64_t pstride, const double *data, int64_t dstride,
-                          cx<T> *mats, int64_t block) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(64) void k_prepare(const DGate *gates, const double2 *fixed, const DSlot *slots, int nslots,
+                                                const double *params, int64_t pstride, const double *data,
+                                                int64_t dstride, cx<T> *mats, int64_t block) {
     const int64_t b = blockIdx.y;
-    if (s >= nslots) return;
-    const DSlot sl = slots[s];
-    prepare_slot<T>(gates, fixed, sl, params ? params + b * pstride : nullptr, data ? data + b * dstride : nullptr,
-                    mats + b * block + sl.off);
+    prepare_slots<T>(gates, fixed, slots, blockIdx.x * blockDim.x + threadIdx.x, nslots,
+                     params ? params + b * pstride : nullptr, data ? data + b * dstride : nullptr, mats + b * block);
 }
 
 // Uneven batches: the slots of every circuit in one launch (blockIdx.y =
 // circuit entry); matrices at ws + mats_off, parameters at params + par_off.
 template <typename T>
-__global__ void k_prepare_multi(const MPrep *ents, const double *params, char *ws) {
-    const MPrep E = ents[blockIdx.y];
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= E.nslots) return;
-    const DSlot sl = E.slots[s];
-    prepare_slot<T>(E.gates, E.fixed, sl, params ? params + E.par_off : nullptr, nullptr,
-                    (cx<T> *)(ws + E.mats_off) + sl.off);
+__global__ __launch_bounds__(64) void k_prepare_multi(const MPrep *ents, const double *params, char *ws) {
+    const MPrep &E = ents[blockIdx.y];
+    if ((int)(blockIdx.x * blockDim.x) >= E.nslots) return;
+    prepare_slots<T>(E.gates, E.fixed, E.slots, blockIdx.x * blockDim.x + threadIdx.x, E.nslots,
+                     params ? params + E.par_off : nullptr, nullptr, (cx<T> *)(ws + E.mats_off));
 }
 
 // One dense block per workgroup, one column per thread: the column starts
