@@ -126,7 +126,9 @@ typedef struct {
                              state sweep; 0: the plain path, one kernel launch per gate */
     int32_t tile_bits;    /* register-resident wires per tile: 0 = auto (5 for complex64,
                              4 for complex128; with jit 6 and 5); 1..6 (complex128: 1..5;
-                             6 only with jit, else 5 is used) */
+                             6 only with jit, else 5 is used).  With jit and 0, tiles of 10 to
+                             31 qubits are shared by the waves of a workgroup and hold two bits
+                             more in all; a given value asks for one-wave tiles of that size */
     int32_t fold_init;    /* 1 (default): fold the leading one-qubit gates of every wire into
                              the initial product-state write when applying from |0..0> */
     int32_t dense_fuse;   /* 0 (default): register tiles; 4 or 5: the forward sweep groups gates
@@ -175,8 +177,9 @@ typedef struct {
     int64_t adj_steps;        /* sweeps of the (state, adjoint) pair in dq_adjoint_grad */
     int64_t folded_gates;     /* gates folded into the initial product state */
     int64_t grad_gates;       /* gate occurrences that carry a gradient */
-    int32_t tile_bits;        /* register bits of the forward tiles */
-    int32_t adj_tile_bits;    /* register bits of the adjoint tiles */
+    int32_t tile_bits;        /* register bits of a one-wave forward tile (workgroup tiles hold two
+                                 bits more, spread over registers and waves: see dq_plan_describe) */
+    int32_t adj_tile_bits;    /* the same of the adjoint tiles */
     int32_t layout_swaps;     /* transpositions of the chosen qubit layout (0: canonical) */
     int32_t pad;
     /* register-tile operations of the forward program (index 0) and the
@@ -197,9 +200,9 @@ dq_status dq_plan_create(dq_plan *out, int32_t nqubits, const dq_gate *gates, in
 void dq_plan_destroy(dq_plan plan);
 dq_status dq_plan_get_stats(dq_plan plan, dq_plan_stats *out);
 /* Text description of the forward and adjoint programs, one line per step:
- * "<fwd|adj> <index> tile R=.. lbits=.. rbits=.. ops=kind:q0:q1:gen:slot:lslot;..."
+ * "<fwd|adj> <index> tile R=.. lbits=.. rbits=.. [wbits=..] ops=kind:q0:q1:gen:slot:lslot;..."
  * for register-tile passes (q = tile-local bit: < 6 lane, else register
- * q - 6), "<fwd|adj> <index> sweep kind=.. k=.. bits=.. slot=.. gen=.. gslot=.."
+ * q - 6, and from 6 + R on the wave bits of a workgroup tile), "<fwd|adj> <index> sweep kind=.. k=.. bits=.. slot=.. gen=.. gslot=.."
  * for whole-state sweeps.  Writes at most cap bytes including the
  * terminating NUL; *needed (nullable) receives the full size.  Host only. */
 dq_status dq_plan_describe(dq_plan plan, char *buf, size_t cap, size_t *needed);

@@ -232,8 +232,10 @@ bool jit_load(const std::vector<std::string> &names, const std::vector<std::stri
             }
             E.mod[dev] = m;
             it = E.fn.emplace(dev, f).first;
-            int per_cu = 0, cus = 0;
-            if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64, 0) != hipSuccess || per_cu < 1)
+            int per_cu = 0, cus = 0, threads = 64;   // a kernel's launch bounds: one wave, or a workgroup tile's waves
+            if (hipFuncGetAttribute(&threads, HIP_FUNC_ATTRIBUTE_MAX_THREADS_PER_BLOCK, f) != hipSuccess || threads < 64)
+                threads = 64;
+            if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, 0) != hipSuccess || per_cu < 1)
                 per_cu = 2;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
                 cus = 256;
@@ -244,19 +246,21 @@ bool jit_load(const std::vector<std::string> &names, const std::vector<std::stri
     return true;
 }
 
-int jit_resident(hipFunction_t f, size_t lds) {
+int jit_resident(hipFunction_t f, int threads, size_t lds) {
     int dev = 0, per_cu = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64, lds) != hipSuccess || per_cu < 1) return 0;
+    if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, lds) != hipSuccess || per_cu < 1) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return 0;
     return per_cu * cus;
 }
 
 hipError_t jit_launch(hipFunction_t f, const std::string &name, const TileArgs &a, bool adj, hipStream_t s) {
     void *args[] = {(void *)&a};
+    const unsigned threads = 64u << a.wb;
     if (adj) {
-        const size_t lds = sizeof(double) * 64 * (a.nlslots > 0 ? a.nlslots : 1);
-        return hipModuleLaunchKernel(f, (unsigned)a.wps, (unsigned)a.batch, 1, 64, 1, 1, (unsigned)lds, s, args, nullptr);
+        // (workgroup tiles hold their accumulators in static LDS)
+        const size_t lds = a.wb ? 0 : sizeof(double) * 64 * (a.nlslots > 0 ? a.nlslots : 1);
+        return hipModuleLaunchKernel(f, (unsigned)a.wps, (unsigned)a.batch, 1, threads, 1, 1, (unsigned)lds, s, args, nullptr);
     }
     int resident = 0;
     {
@@ -269,13 +273,13 @@ hipError_t jit_launch(hipFunction_t f, const std::string &name, const TileArgs &
             if (r != it->second.resident.end()) resident = r->second;
         }
     }
-    const int64_t tiles = a.batch << (a.n - 6 - a.R);
+    const int64_t tiles = a.batch << (a.n - 6 - a.R - a.wb);
     // four grid-stride waves per resident slot: the waves that wait for a
     // slot fill the ramp-down of the ones before them (a 32-qubit forward
     // pass: 14.26 against 14.61 ms with one wave per slot)
     const int64_t cap = 4 * (resident > 0 ? resident : 4096);
     const unsigned g = (unsigned)(tiles < cap ? (tiles < 1 ? 1 : tiles) : cap);
-    return hipModuleLaunchKernel(f, g, 1, 1, 64, 1, 1, 0, s, args, nullptr);
+    return hipModuleLaunchKernel(f, g, 1, 1, threads, 1, 1, 0, s, args, nullptr);
 }
 
 }  // namespace dq

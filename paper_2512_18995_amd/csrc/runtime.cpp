@@ -144,7 +144,9 @@ struct Step {
     int R = 0;
     int32_t rbits[MAX_TILE_R] = {0};
     int32_t lbits[3] = {0};
-    int32_t tbits[MAX_TILE_R + 3] = {0};
+    int wb = 0;                     // wave bits of a workgroup tile (compiled passes only)
+    int32_t wbits[MAX_TILE_W] = {0};
+    int32_t tbits[MAX_TILE_R + 3 + MAX_TILE_W] = {0};
     int64_t op0 = 0, nops = 0;      // into plan.ops
     int64_t ls0 = 0, nls = 0;       // into plan.lsg
     int k = 0;
@@ -210,6 +212,9 @@ struct dq_plan_s {
     std::vector<int64_t> fold_off;      // per physical bit: slot offset of the folded column, -1 none
     int64_t folded_gates = 0;
     int R_fwd = 0, R_adj = 0;
+    int Rt_fwd = 0, Rt_adj = 0;                // register bits of the tiles as planned
+    int wb_fwd = 0, wb_adj = 0;                // and their wave bits
+    bool one_wave = false;                     // no workgroup tiles (complete_plan)
     int32_t ngrad = 0;
     // the adjoint's gate order and gradient slots, and the sizes of what its
     // planner appends to (slots, ops, lsg, factors, blocks, block), so that
@@ -302,7 +307,7 @@ constexpr double kStreamBytes = 256.0 * 1024 * 1024;
 struct Planner {
     dq_plan_s &p;
     bool adjoint;
-    int R;
+    int R, W;               // register bits and wave bits of a tile
     // Physical bits 3 and 4 in every tile of a large state: each group of 16
     // lanes then reads 128 contiguous bytes and each register pair 256.
     // Tiles whose bits are all high physical bits scatter every wave's
@@ -315,7 +320,9 @@ struct Planner {
     // kernel with 64 registers per lane keeps its tile in scratch memory
     int max_ops = 0;        // 0: no limit
     bool fusing = false;    // one-qubit gates on a wire fold into one operation (forward)
-    explicit Planner(dq_plan_s &pl, bool adj, int r) : p(pl), adjoint(adj), R(r) {
+    int cap;                // tile bits above physical bit 2
+    explicit Planner(dq_plan_s &pl, bool adj)
+        : p(pl), adjoint(adj), R(adj ? pl.Rt_adj : pl.Rt_fwd), W(adj ? pl.wb_adj : pl.wb_fwd), cap(R + 3 + W) {
         if (p.opt.jit && R > 0) max_ops = (int)(kJitMaxWork >> R);
         const int64_t state_bytes = (int64_t)(p.dbl ? 16 : 8) << p.n;
         // auto: bits 3 and 4 in both directions.  Pinning bit 3 alone frees
@@ -324,7 +331,7 @@ struct Planner {
         // pages landed (27 to 37 ms per 32-qubit pass between runs of one
         // plan, against 25 ms with 256-byte pieces)
         const int want = p.opt.low_bits > 0 ? p.opt.low_bits - 1 : 2;   // physical bits 3.. to pin
-        if (want > 0 && R >= 2 && p.n >= R + 8 && state_bytes >= (int64_t(128) << 20))
+        if (want > 0 && R >= 2 && p.n >= cap + 5 && state_bytes >= (int64_t(128) << 20))
             pinned = want >= 2 ? (1ull << 3) | (1ull << 4) : (1ull << 3);
     }
 
@@ -338,7 +345,7 @@ struct Planner {
         if (G.op == OP_UNITARY && G.nq != 1) return false;
         int hi = 0;
         for (int i = 0; i < G.nq; ++i) hi += G.bits[i] >= 3;
-        return hi <= R + 3;
+        return hi <= cap;
     }
     bool diff(int g) const { return adjoint && p.gates[g].src != SRC_NONE && is_rotation(p.gates[g].op); }
     // With float64 arithmetic in compiled passes a diagonal one-qubit gate
@@ -367,7 +374,7 @@ struct Planner {
             gbits(rem[seed], q, nq);
             for (int i = 0; i < nq; ++i)
                 if (q[i] >= 3) S |= 1ull << q[i];
-            if (popc(S) > R + 3) return out;
+            if (popc(S) > cap) return out;
         }
         for (size_t r = 0; r < rem.size(); ++r) {
             const int g = rem[r];
@@ -378,7 +385,7 @@ struct Planner {
                 Q |= 1ull << q[i];
                 if (q[i] >= 3) need |= 1ull << q[i];
             }
-            if ((Q & blocked) || !tile_ok(g) || (diff(g) && lslots >= 32) || popc(S | need) > R + 3) {
+            if ((Q & blocked) || !tile_ok(g) || (diff(g) && lslots >= 32) || popc(S | need) > cap) {
                 blocked |= Q;
                 continue;
             }
@@ -544,6 +551,79 @@ struct Planner {
         std::swap(lanes[out], *hi);
     }
 
+    // The bits whose amplitudes gate g exchanges (the others only control or
+    // carry diagonal factors).
+    int moved_bits(int g, int *q) const {
+        const DGate &G = p.gates[g];
+        if (is_diag1(G.op) || G.op == OP_CZ || G.op == OP_CP || G.op == OP_RZZ) return 0;
+        if (G.op == OP_CNOT) {
+            q[0] = G.bits[1];
+            return 1;
+        }
+        for (int i = 0; i < G.nq; ++i) q[i] = G.bits[i];
+        return G.nq;
+    }
+
+    // One wave's tile: lane bits 3..5 are the three free bits that see the
+    // fewest data-moving ops (those need cross-lane shuffles); the rest are
+    // register bits.
+    void place_wave_tile(uint64_t S, const std::vector<int> &best, const std::vector<int> &rem, std::vector<int> &lanes,
+                         std::vector<int> &regs) const {
+        int moves[64] = {0}, q[5];
+        for (int r : best)
+            for (int i = moved_bits(rem[r], q) - 1; i >= 0; --i) moves[q[i]] += 1;
+        std::vector<int> freeb;
+        for (int b = 3; b < p.n; ++b)
+            if (S >> b & 1) freeb.push_back(b);
+        std::stable_sort(freeb.begin(), freeb.end(), [&](int x, int y) { return moves[x] < moves[y]; });
+        if (pinned) {   // lane bit 3 = physical bit 3, physical bit 4 (if pinned) a register bit
+            const bool p4 = (pinned >> 4) & 1;
+            std::vector<int> rest;
+            for (int b : freeb)
+                if (b != 3 && !(p4 && b == 4)) rest.push_back(b);
+            freeb.assign({3});
+            freeb.insert(freeb.end(), rest.begin(), rest.begin() + 2);
+            if (p4) freeb.push_back(4);
+            freeb.insert(freeb.end(), rest.begin() + 2, rest.end());
+        }
+        lanes.assign(freeb.begin(), freeb.begin() + 3);
+        regs.assign(freeb.begin() + 3, freeb.end());
+        far_register_rule(lanes, regs, moves);
+        std::sort(lanes.begin(), lanes.end());
+        std::sort(regs.begin(), regs.end());
+    }
+
+    // A workgroup's tile, as it is loaded: register bits are the bits that
+    // the pass's first gates exchange, in gate order, but never physical bits
+    // 3 and 4 (with those on lanes a wave reads whole cache lines).  Bits of
+    // either kind are listed in the order the pass uses them, so that passes
+    // with the same gates on other wires share one kernel.
+    void place_workgroup_tile(uint64_t S, const std::vector<int> &best, const std::vector<int> &rem,
+                              std::vector<int> &lanes, std::vector<int> &regs, std::vector<int> &waves) const {
+        uint64_t in = 0;
+        int q[5];
+        auto take = [&](std::vector<int> &to, int b) {
+            if (!((S >> b) & 1) || ((in >> b) & 1)) return;
+            in |= 1ull << b;
+            to.push_back(b);
+        };
+        for (int r : best)
+            for (int i = 0, m = moved_bits(rem[r], q); i < m && (int)regs.size() < R; ++i)
+                if (q[i] > 4) take(regs, q[i]);
+        for (int b = p.n - 1; b >= 3 && (int)regs.size() < R; --b) take(regs, b);   // pad from the top
+        take(lanes, 3);
+        take(lanes, 4);
+        std::vector<int> rest;
+        for (int r : best) {
+            int nq;
+            gbits(rem[r], q, nq);
+            for (int i = 0; i < nq; ++i)
+                if (q[i] >= 3) take(rest, q[i]);
+        }
+        for (int b = 3; b < p.n; ++b) take(rest, b);
+        for (int b : rest) (lanes.size() < 3 ? lanes : waves).push_back(b);
+    }
+
     static bool real1(int op) { return op == OP_RY || op == OP_H || op == OP_X || op == OP_Z; }
 
     void plan(Program &prog, std::vector<int> order, bool fuse_1q) {
@@ -585,44 +665,18 @@ struct Planner {
                 rem.erase(rem.begin());
                 continue;
             }
-            // pad the free set to exactly R + 3 bits
-            for (int b = 3; b < p.n && __builtin_popcountll(bestS) < R + 3; ++b) bestS |= 1ull << b;
-            // lane bits 3..5: the three free bits that see the fewest
-            // data-moving ops (those need cross-lane shuffles); the rest are
-            // register bits
-            int moves[64] = {0};
-            for (int r : best) {
-                const DGate &G = p.gates[rem[r]];
-                const bool diag = is_diag1(G.op) || G.op == OP_CZ || G.op == OP_CP || G.op == OP_RZZ;
-                if (diag) continue;
-                if (G.op == OP_CNOT) moves[G.bits[1]] += 1;
-                else
-                    for (int i = 0; i < G.nq; ++i) moves[G.bits[i]] += 1;
-            }
-            std::vector<int> freeb;
-            for (int b = 3; b < p.n; ++b)
-                if (bestS >> b & 1) freeb.push_back(b);
-            std::stable_sort(freeb.begin(), freeb.end(), [&](int x, int y) { return moves[x] < moves[y]; });
-            if (pinned) {   // lane bit 3 = physical bit 3, physical bit 4 (if pinned) a register bit
-                const bool p4 = (pinned >> 4) & 1;
-                std::vector<int> rest;
-                for (int b : freeb)
-                    if (b != 3 && !(p4 && b == 4)) rest.push_back(b);
-                freeb.assign({3});
-                freeb.insert(freeb.end(), rest.begin(), rest.begin() + 2);
-                if (p4) freeb.push_back(4);
-                freeb.insert(freeb.end(), rest.begin() + 2, rest.end());
-            }
+            // pad the free set to exactly `cap` bits
+            for (int b = 3; b < p.n && __builtin_popcountll(bestS) < cap; ++b) bestS |= 1ull << b;
             Step st;
             st.kind = ST_TILE;
             st.R = R;
+            st.wb = W;
             int local[64];
             for (int b = 0; b < 64; ++b) local[b] = -1;
             for (int b = 0; b < 3; ++b) local[b] = b;
-            std::vector<int> lanes(freeb.begin(), freeb.begin() + 3), regs(freeb.begin() + 3, freeb.end());
-            far_register_rule(lanes, regs, moves);
-            std::sort(lanes.begin(), lanes.end());
-            std::sort(regs.begin(), regs.end());
+            std::vector<int> lanes, regs, waves;
+            if (W == 0) place_wave_tile(bestS, best, rem, lanes, regs);
+            else place_workgroup_tile(bestS, best, rem, lanes, regs, waves);
             for (int k = 0; k < 3; ++k) {
                 st.lbits[k] = lanes[k];
                 local[lanes[k]] = 3 + k;
@@ -631,9 +685,12 @@ struct Planner {
                 st.rbits[k] = regs[k];
                 local[regs[k]] = 6 + k;
             }
-            std::vector<int> all(freeb);
-            std::sort(all.begin(), all.end());
-            for (int k = 0; k < R + 3; ++k) st.tbits[k] = all[k];
+            for (int k = 0; k < W; ++k) {
+                st.wbits[k] = waves[k];
+                local[waves[k]] = 6 + R + k;
+            }
+            for (int k = 0, b = 3; b < p.n; ++b)
+                if (bestS >> b & 1) st.tbits[k++] = b;
             st.op0 = (int64_t)p.ops.size();
             st.ls0 = (int64_t)p.lsg.size();
             std::vector<int> last_op(64, -1);     // per physical bit: index (in p.ops) of the last op touching it
@@ -743,6 +800,32 @@ int default_R(const dq_plan_s &p) {
     return R < 0 ? 0 : R;
 }
 
+// Tiles shared by the waves of a workgroup: compiled passes whose tile shape
+// the caller leaves to the planner.  Measured against one-wave tiles (forward
+// + adjoint of the ring ansatz, complex64, 6 layers unless stated): 10 to 14
+// qubits, where most of the state is one tile, 0.159 -> 0.112 ms (10) to
+// 0.393 -> 0.338 ms (14), 200 samples 0.179 -> 0.131 to 0.695 -> 0.520 ms;
+// 15 to 17 qubits, 64 samples, 0.656 -> 0.483, 0.889 -> 0.686, 1.376 ->
+// 1.226 ms; 31 qubits, 4 layers, 417 -> 343 ms (float64 arithmetic 506 -> 498).
+// Registers of 32 qubits and more keep one-wave tiles: there the gain is 3 %
+// (734 -> 712 ms, float64 arithmetic 1026 -> 985 ms).  Below 10 qubits a
+// tile would leave fewer than two register bits per wave.
+bool workgroup_tiles(const dq_plan_s &p) {
+    return p.opt.fusion && p.opt.jit && p.opt.tile_bits == 0 && !p.opt.dense_fuse && !p.one_wave && p.n >= 10 &&
+           p.n <= 31;
+}
+// Two bits more than the one-wave tile with R register bits.  float32
+// arithmetic: eight waves with one register bit less each, so that four waves
+// per SIMD stay resident (20 qubits, 16 samples: 6.03 ms against 7.55 with
+// four waves and two per SIMD).  float64 arithmetic: four waves, because an
+// exchange through LDS moves twice the bytes and fewer register bits need
+// more of them (28 qubits, 8 layers: 101 ms against 115.6 with eight waves).
+void workgroup_shape(const dq_plan_s &p, int R, int &Rt, int &wb) {
+    const int T = std::min(p.n, 6 + R + 2);
+    wb = std::min<int>(p.mdbl ? 2 : 3, T - 8);
+    Rt = T - 6 - wb;
+}
+
 // (Re)plan the adjoint program, at most `cap` operations per tile pass when
 // cap > 0; returns its number of steps.
 size_t plan_adjoint(dq_plan_s &p, int cap) {
@@ -754,7 +837,7 @@ size_t plan_adjoint(dq_plan_s &p, int cap) {
     p.blocks.resize(m[4]);
     p.block = (int64_t)m[5];
     p.adj = Program();
-    Planner pl(p, true, p.R_adj);
+    Planner pl(p, true);
     if (cap > 0) pl.max_ops = pl.max_ops > 0 ? std::min(pl.max_ops, cap) : cap;
     pl.gslot_of = p.adj_gslot;
     pl.plan(p.adj, p.adj_rev, false);
@@ -804,6 +887,13 @@ dq_status build_plan(dq_plan_s &p) {
     if (!p.opt.jit && ra > (p.dbl ? 3 : 4)) ra = p.dbl ? 3 : 4;
     if (ra > p.n - 6) ra = p.n - 6;
     p.R_adj = fused && ra > 0 ? ra : 0;
+    p.wb_fwd = p.wb_adj = 0;
+    p.Rt_fwd = p.R_fwd;
+    p.Rt_adj = p.R_adj;
+    if (workgroup_tiles(p)) {
+        workgroup_shape(p, p.R_fwd, p.Rt_fwd, p.wb_fwd);
+        if (p.opt.adj_tile_bits == 0) workgroup_shape(p, p.R_adj, p.Rt_adj, p.wb_adj);
+    }
     // gradient slots: every differentiable gate occurrence, in gate order
     std::vector<int> gslot(G_all, -1);
     p.ngrad = 0;
@@ -838,7 +928,7 @@ dq_status build_plan(dq_plan_s &p) {
         std::vector<int> full;
         for (int g = G; g < G_all; ++g) full.push_back(g);
         full.insert(full.end(), order.begin(), order.end());
-        Planner pl(p, false, p.R_fwd);
+        Planner pl(p, false);
         pl.gslot_of = gslot;
         if (dense) pl.plan_dense(p.fwd_full, full, dense_k);
         else pl.plan(p.fwd_full, full, true);
@@ -874,7 +964,7 @@ dq_status build_plan(dq_plan_s &p) {
             std::vector<int> rest;
             for (int g = 0; g < G; ++g)
                 if (!folded[g]) rest.push_back(g);
-            Planner pl(p, false, p.R_fwd);
+            Planner pl(p, false);
             pl.gslot_of = gslot;
             const int64_t lo = (int64_t)p.slots.size() - (int64_t)std::count_if(p.fold_off.begin(), p.fold_off.end(),
                                                                                 [](int64_t o) { return o >= 0; });
@@ -910,6 +1000,244 @@ bool has_matrix(int kind) {
     return kind == TK_1Q || kind == TK_1QDIAG || kind == TK_2QDIAG || kind == TK_1QREAL || kind == TK_1QRX;
 }
 
+// ---------------------------------------------------------------- workgroup tiles
+// The operations of a workgroup tile's pass in execution order, at the
+// positions they have when they run, with layout exchanges between them
+// (kind TK_XCHG, q0 = the exchange's number), and the text of the exchanges'
+// index masks (struct X<k>) and of the layout the pass stores from (Out).
+enum : int32_t { TK_XCHG = 64 };
+struct WideSchedule {
+    std::vector<TOp> items;
+    std::string layouts;
+    int exchanges = 0;
+};
+
+// Operations are taken in program order per bit (two that share a bit keep
+// their order; the rest commute, gradient terms included: conjugating <l|G|p>
+// by a gate on other bits leaves it unchanged).  In a layout every operation
+// runs whose exchanged bits are register bits; diagonal operations and
+// controls may sit anywhere.  When none is left that can, either the tile
+// moves to the layout whose register bits let most of the following
+// operations run, or operations on lane bits run as cross-lane exchanges; a
+// small search over these choices minimises the cost, in VALU instructions
+// per amplitude and state: an exchange through LDS costs what about `kx`
+// instructions do (its LDS time and barriers), a cross-lane operation what its
+// lane moves add to the register form.
+struct WideScheduler {
+    int R, W, TB, hold, dbl;
+    const std::vector<TOp> &ops;
+    struct State {
+        std::vector<char> done;
+        int at[32];     // tile bit -> position
+        double cost = 0;
+        std::vector<TOp> items;
+        std::vector<std::vector<int>> lay;   // layouts (position -> tile bit), the first is the identity
+        int left = 0;
+    };
+    State best;
+    bool found = false;
+    int nodes = 0;
+
+    bool reg(int p) const { return p >= 6 && p < 6 + R; }
+    static uint64_t bits(const TOp &o) {
+        const bool two = o.kind == TK_CNOT || o.kind == TK_CZ || o.kind == TK_2QDIAG || o.kind == TK_SWAP;
+        return (1ull << o.q0) | (two ? 1ull << o.q1 : 0);
+    }
+    // tile bits an operation exchanges
+    static uint64_t moved(const TOp &o) {
+        switch (o.kind) {
+        case TK_1QDIAG: case TK_CZ: case TK_2QDIAG: return 0;
+        case TK_CNOT: return 1ull << o.q1;
+        case TK_SWAP: return (1ull << o.q0) | (1ull << o.q1);
+        default: return 1ull << o.q0;
+        }
+    }
+    // what the lane moves of an operation on a lane position add (32-bit words moved)
+    double lane_cost(const State &s, const TOp &o) const {
+        static const int word[6] = {1, 1, 2, 2, 4, 4};
+        double c = 0;
+        const int wide = dbl ? 4 : 2;
+        for (uint64_t mv = moved(o); mv; mv &= mv - 1) {
+            const int q = s.at[__builtin_ctzll(mv)];
+            if (q < 6) c += word[q] * wide + (o.kind == TK_CNOT || o.kind == TK_SWAP ? wide : 0);
+        }
+        return o.kind == TK_SWAP ? 2 * c : c;
+    }
+    bool runs(const State &s, const TOp &o, bool lanes) const {
+        for (uint64_t mv = moved(o); mv; mv &= mv - 1) {
+            const int q = s.at[__builtin_ctzll(mv)];
+            if (!reg(q) && !(lanes && q < 6)) return false;
+        }
+        return true;
+    }
+    void emit(State &s, bool lanes) const {
+        uint64_t blocked = 0;
+        for (size_t k = 0; k < ops.size(); ++k) {
+            if (s.done[k]) continue;
+            if ((bits(ops[k]) & blocked) || !runs(s, ops[k], lanes)) {
+                blocked |= bits(ops[k]);
+                continue;
+            }
+            TOp o = ops[k];
+            if (lanes) s.cost += lane_cost(s, o);
+            const bool two = bits(o) != (1ull << o.q0);
+            o.q0 = s.at[o.q0];
+            if (two) o.q1 = s.at[o.q1];
+            s.items.push_back(o);
+            s.done[k] = 1;
+            --s.left;
+        }
+    }
+    // the register bits that let most of the next operations run
+    uint64_t next_regs(const State &s, bool spare_low) const {
+        uint64_t S = 0, blocked = 0;
+        const uint64_t low = (1ull << hold) - 1;
+        for (size_t k = 0; k < ops.size(); ++k) {
+            if (s.done[k]) continue;
+            const uint64_t need = S | moved(ops[k]);
+            if ((bits(ops[k]) & blocked) || __builtin_popcountll(need) > R || (spare_low && (moved(ops[k]) & low))) {
+                blocked |= bits(ops[k]);
+                continue;
+            }
+            S = need;
+        }
+        return S;
+    }
+    void exchange(State &s, uint64_t S) const {
+        const std::vector<int> &from = s.lay.back();
+        // pad with the bits that are in registers now, then any but the low ones
+        for (int p = 6; p < 6 + R && __builtin_popcountll(S) < R; ++p)
+            if (from[p] >= hold) S |= 1ull << from[p];
+        for (int b = TB - 1; b >= 0 && __builtin_popcountll(S) < R; --b) S |= 1ull << b;
+        std::vector<int> to(TB, -1);
+        uint64_t placed = 0;
+        auto put = [&](int p, int b) {
+            to[p] = b;
+            placed |= 1ull << b;
+        };
+        for (int p = 0; p < 6; ++p)
+            if (!((S >> p) & 1)) put(p, p);
+        for (int p = 6; p < 6 + R; ++p)   // register bits stay where they are
+            if ((S >> from[p]) & 1) put(p, from[p]);
+        for (int p = 6; p < 6 + R; ++p)
+            for (int b = 0; b < TB && to[p] < 0; ++b)
+                if (((S >> b) & 1) && !((placed >> b) & 1)) put(p, b);
+        for (int p = 0; p < TB; ++p)
+            for (int b = 0; b < TB && to[p] < 0; ++b)
+                if (!((placed >> b) & 1)) put(p, b);
+        TOp x{};
+        x.kind = TK_XCHG;
+        x.q0 = (int)s.lay.size() - 1;
+        x.lslot = -1;
+        s.items.push_back(x);
+        s.lay.push_back(to);
+        for (int p = 0; p < TB; ++p) s.at[to[p]] = p;
+        s.cost += dbl ? 36.0 : 18.0;
+    }
+    bool storable(const State &s) const {
+        for (int p = 0; p < hold; ++p)
+            if (s.at[p] != p) return false;
+        return true;
+    }
+    void search(State s) {
+        emit(s, false);
+        if (s.left == 0) {
+            if (!storable(s)) exchange(s, 0);
+            if (!found || s.cost < best.cost) {
+                best = std::move(s);
+                found = true;
+            }
+            return;
+        }
+        if ((found && s.cost >= best.cost) || ++nodes > 2000) {
+            if (found) return;
+        }
+        const uint64_t a = next_regs(s, false), b = next_regs(s, true);
+        {
+            State t = s;
+            exchange(t, a);
+            search(std::move(t));
+        }
+        if (b && b != a) {
+            State t = s;
+            exchange(t, b);
+            search(std::move(t));
+        }
+        State t = s;
+        emit(t, true);
+        if (t.left < s.left) search(std::move(t));
+    }
+};
+
+WideSchedule wide_schedule(const dq_plan_s &p, const Step &S, bool adj) {
+    (void)adj;
+    const std::vector<TOp> ops(p.ops.begin() + S.op0, p.ops.begin() + S.op0 + S.nops);
+    WideScheduler W{S.R, S.wb, 6 + S.R + S.wb, 3, p.mdbl, ops, {}, false, 0};
+    while (W.hold < 6 && S.lbits[W.hold - 3] == W.hold) ++W.hold;   // lanes that continue the low bits
+    W.hold = std::min(W.hold, 5);
+    WideScheduler::State s;
+    s.done.assign(ops.size(), 0);
+    s.left = (int)ops.size();
+    std::vector<int> id(W.TB);
+    for (int q = 0; q < W.TB; ++q) s.at[q] = id[q] = q;
+    s.lay.push_back(id);
+    W.search(s);
+    const WideScheduler::State &r = W.best;
+    WideSchedule out;
+    out.items = r.items;
+    out.exchanges = (int)r.lay.size() - 1;
+    auto list = [](const std::vector<int> &v) {
+        std::string t;
+        for (size_t i = 0; i < v.size(); ++i) t += (i ? ", " : "") + std::to_string(v[i]);
+        return t;
+    };
+    for (int k = 0; k < out.exchanges; ++k) {
+        // index masks of the tile bits: the common lane bits and the new
+        // layout's other lane bits are index bits 0..5; each of the old
+        // layout's other lane bits is XORed onto one of the latter beside an
+        // index bit of its own
+        const std::vector<int> &F = r.lay[(size_t)k], &G = r.lay[(size_t)k + 1];
+        std::vector<int> M(W.TB, 0), f, g;
+        int lowb = 0, high = 6;
+        for (int i = 0; i < 6; ++i) {
+            const bool common = std::find(G.begin(), G.begin() + 6, F[i]) != G.begin() + 6;
+            if (common) M[F[i]] = 1 << lowb++;
+            else f.push_back(F[i]);
+            if (std::find(F.begin(), F.begin() + 6, G[i]) == F.begin() + 6) g.push_back(G[i]);
+        }
+        for (size_t i = 0; i < f.size(); ++i) {
+            M[g[i]] = 1 << lowb;
+            M[f[i]] = (1 << lowb++) | (1 << high++);
+        }
+        for (int q = 0; q < W.TB; ++q)
+            if (M[q] == 0) M[q] = 1 << high++;
+        if (lowb != 6 || high != W.TB) throw std::runtime_error("workgroup tile: exchange masks do not cover the tile");
+        std::vector<int> w(W.TB), rd(W.TB);
+        for (int q = 0; q < W.TB; ++q) {
+            w[q] = M[F[q]];
+            rd[q] = M[G[q]];
+        }
+        const std::string n = std::to_string(W.TB), R = std::to_string(S.R);
+        // index bits that a lane or wave bit touches
+        auto low = [&](const char *name, const std::vector<int> &m) {
+            int x = 0;
+            for (int q = 0; q < W.TB; ++q)
+                if (q < 6 || q >= 6 + S.R) x |= m[q];
+            return std::string("    static constexpr int ") + name + "() { return " + std::to_string(x) + "; }\n";
+        };
+        auto fold = [&](const char *name, const char *arr) {
+            return std::string("    static constexpr int ") + name + "(int i) { int x = 0; for (int k = 0; k < " + R +
+                   "; ++k) if ((i >> k) & 1) x ^= " + arr + "[6 + k]; return x; }\n";
+        };
+        out.layouts += "struct X" + std::to_string(k) + " {\n    static constexpr int w[" + n + "] = {" + list(w) +
+                       "};\n    static constexpr int r[" + n + "] = {" + list(rd) + "};\n" + fold("wreg", "w") +
+                       fold("rreg", "r") + low("wlow", w) + low("rlow", rd) + "};\n";
+    }
+    out.layouts += "struct Out {\n    static constexpr int t[" + std::to_string(W.TB) + "] = {" + list(r.lay.back()) +
+                   "};\n    static constexpr int at(int p) { return t[p]; }\n};\n";
+    return out;
+}
+
 std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) {
     s0 = -1;
     for (int64_t i = 0; i < S.nops; ++i) {
@@ -925,12 +1253,32 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
     // occupancy target (waves per SIMD): two while a lane holds up to 64
     // complex64 amplitudes of one state (32 of each of two in the adjoint)
     const int rb = NR * (p.mdbl ? 8 : 4);
-    const int W = adj ? (rb >= 256 ? 1 : (rb >= 64 ? 2 : 4)) : (rb >= 512 ? 1 : (rb >= 128 ? 2 : 3));
+    const int W = S.wb ? (p.mdbl ? 2 : 4) : adj ? (rb >= 256 ? 1 : (rb >= 64 ? 2 : 4)) : (rb >= 512 ? 1 : (rb >= 128 ? 2 : 3));
     char line[256];
     std::string b;
-    snprintf(line, sizeof line, "__launch_bounds__(64, %d) void @NAME@(dq::TileArgs a) {\n", W);
+    // the operations at their positions: a workgroup tile's pass interleaves
+    // them with exchanges of its layout
+    WideSchedule sch;
+    if (S.wb) sch = wide_schedule(p, S, adj);
+    else sch.items.assign(p.ops.begin() + S.op0, p.ops.begin() + S.op0 + S.nops);
+    auto is_reg = [&](int q) { return q >= 6 && q < 6 + R; };
+    if (S.wb) b += sch.layouts;
+    b += "extern \"C\" __global__ ";
+    snprintf(line, sizeof line, "__launch_bounds__(%d, %d) void @NAME@(dq::TileArgs a) {\n", 64 << S.wb, W);
     b += line;
-    if (adj) {
+    if (S.wb) {
+        snprintf(line, sizeof line, "    __shared__ %s buf[%d];\n", T, sch.exchanges ? NS << (6 + R + S.wb) : 1);
+        b += line;
+        if (adj) {
+            snprintf(line, sizeof line,
+                     "    __shared__ double ac[%d];\n"
+                     "    dq::jit_adj_wide<%s, %d, %d, %s, %s, Out>(a, ac, [&](auto &v, auto m, int lane, int ln_, int wv_) {\n",
+                     (int)std::max<int64_t>(S.nls, 1) << (S.wb + 3), T, R, S.wb, nt, SS);
+        } else {
+            snprintf(line, sizeof line, "    dq::jit_fwd_wide<%s, %d, %d, %s, %s, Out>(a, [&](auto &v, auto m, int lane) {\n",
+                     T, R, S.wb, nt, SS);
+        }
+    } else if (adj) {
         snprintf(line, sizeof line,
                  "    extern __shared__ double acc[];\n"
                  "    dq::jit_adj<%s, %d, %s, %s>(a, acc, [&](auto &v, auto m, int lane, double *ac) {\n", T, R, nt, SS);
@@ -938,20 +1286,32 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
         snprintf(line, sizeof line, "    dq::jit_fwd<%s, %d, %s, %s>(a, [&](auto &v, auto m, int lane) {\n", T, R, nt, SS);
     }
     b += line;
-    const TOp *ops = p.ops.data() + S.op0;
-    for (int64_t i = 0; i < S.nops;) {
+    // adds `value` to gradient slot `slot`
+    auto add_term = [&](int slot, const std::string &value) {
+        if (S.wb) b += "dq::wide_acc<" + std::to_string(S.wb) + ">(ac, " + std::to_string(slot) + ", ln_, wv_, (double)(" + value + "));\n";
+        else b += "ac[" + std::to_string(slot) + " * 64 + lane] += (double)(" + value + ");\n";
+    };
+    const std::vector<TOp> &ops = sch.items;
+    const int64_t nops = (int64_t)ops.size();
+    for (int64_t i = 0; i < nops;) {
+        if (ops[i].kind == TK_XCHG) {
+            snprintf(line, sizeof line, "        dq::xchg<%s, %d, %d, %d, X%d>(v, buf, lane);\n", T, NS, R, S.wb, ops[i].q0);
+            b += line;
+            ++i;
+            continue;
+        }
         // a run of one-qubit diagonal gates (the RZ of a layer and the like)
         // becomes one product diagonal; diagonal gates commute, so their
         // gradient terms are all taken at the start of the run
         int64_t e = i;
-        while (e < S.nops && ops[e].kind == TK_1QDIAG) ++e;
+        while (e < nops && ops[e].kind == TK_1QDIAG) ++e;
         if (e - i >= 2) {
             b += "        {\n";
             bool anyg = false;
             for (int64_t j = i; j < e; ++j) anyg |= adj && ops[j].lslot >= 0;
             std::vector<int> regk;   // distinct register bits of the run, in first-use order
             for (int64_t j = i; j < e; ++j)
-                if (ops[j].q0 >= 6 && std::find(regk.begin(), regk.end(), ops[j].q0 - 6) == regk.end()) regk.push_back(ops[j].q0 - 6);
+                if (is_reg(ops[j].q0) && std::find(regk.begin(), regk.end(), ops[j].q0 - 6) == regk.end()) regk.push_back(ops[j].q0 - 6);
             if (anyg) {
                 snprintf(line, sizeof line, "            %s sa_, sk_[%d];\n            dq::run_sums<%s, dq::cx<%s>, %d", T,
                          regk.empty() ? 1 : (int)regk.size(), T, T, NR);
@@ -962,13 +1322,13 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
             for (int64_t j = i; j < e; ++j) {
                 const TOp &o = ops[j];
                 if (!adj || o.lslot < 0) continue;
-                if (o.q0 < 6) {
-                    snprintf(line, sizeof line, "            ac[%d * 64 + lane] += (double)(((lane >> %d) & 1) ? -sa_ : sa_);\n", o.lslot, o.q0);
+                b += "            ";
+                if (!is_reg(o.q0)) {
+                    add_term(o.lslot, "((lane >> " + std::to_string(o.q0) + ") & 1) ? -sa_ : sa_");
                 } else {
                     const size_t ri = (size_t)(std::find(regk.begin(), regk.end(), o.q0 - 6) - regk.begin());
-                    snprintf(line, sizeof line, "            ac[%d * 64 + lane] += (double)sk_[%zu];\n", o.lslot, ri);
+                    add_term(o.lslot, "sk_[" + std::to_string(ri) + "]");
                 }
-                b += line;
             }
             // the lane factor fl_ and the ratios r_ are formed in double and
             // rounded once inside diag_run
@@ -978,7 +1338,7 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
             for (int64_t j = i; j < e; ++j) {
                 const TOp &o = ops[j];
                 const long long sl = (long long)(o.slot - s0);
-                if (o.q0 < 6) {
+                if (!is_reg(o.q0)) {
                     snprintf(line, sizeof line, "            fl_ = dq::cmul(fl_, dq::widen(dq::csel(((lane >> %d) & 1) != 0, dq::ldc(m, %lld), dq::ldc(m, %lld))));\n",
                              o.q0, sl + 3, sl);
                 } else {
@@ -1003,9 +1363,9 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
         }
         const TOp &o = ops[i];
         if (adj && o.lslot >= 0) {
-            snprintf(line, sizeof line, "        ac[%d * 64 + lane] += (double)dq::gen_s<%s, %d, %d, %d, %d>(v[0], v[1], lane);\n",
-                     o.lslot, T, NR, o.gen, o.q0, o.q1);
-            b += line;
+            snprintf(line, sizeof line, "dq::gen_s<%s, %d, %d, %d, %d>(v[0], v[1], lane)", T, NR, o.gen, o.q0, o.q1);
+            b += "        ";
+            add_term(o.lslot, line);
         }
         snprintf(line, sizeof line, "        dq::op_s<%s, %d, %d, %d, %d, %d, %lld>(v, m, lane);\n", T, NS, NR, o.kind, o.q0,
                  o.q1, has_matrix(o.kind) ? (long long)(o.slot - s0) : 0ll);
@@ -1029,13 +1389,13 @@ void jit_generate(dq_plan_s &p) {
             // straight-line code: longer passes stay interpreted, except
             // 64-amplitude tiles, which have no interpreted kernel (the
             // planner keeps them within the limit in any case)
-            if (S.R < 6 && S.nops * (int64_t(1) << S.R) > kJitMaxWork) continue;
+            if (S.R < 6 && S.wb == 0 && S.nops * (int64_t(1) << S.R) > kJitMaxWork) continue;
             int64_t s0 = 0;
             const std::string body = pass_body(p, S, adj, s0);
             auto it = index.find(body);
             if (it == index.end()) {
                 const std::string name = jit_key(body);
-                std::string src = "#include \"tile_dev.h\"\nextern \"C\" __global__ " + body;
+                std::string src = "#include \"tile_dev.h\"\n" + body;
                 src.replace(src.find("@NAME@"), 6, name);
                 it = index.emplace(body, (int)p.jnames.size()).first;
                 p.jnames.push_back(name);
@@ -1086,6 +1446,7 @@ dq_plan_s *plan_clone_base(const dq_plan_s &p) {
     q->ndata = p.ndata;
     q->fixed = p.fixed;
     q->user_gates = p.user_gates;
+    q->one_wave = p.one_wave;
     q->entry_gates = 0;
     q->canon = p.canon;
     q->occ_param = p.occ_param;
@@ -1151,6 +1512,33 @@ dq_plan_s *search_layout(dq_plan_s *p_in) {
     return chosen ? chosen.release() : canon.release();
 }
 
+// Programs, layout and kernels of a plan whose gate list is set.  Up to 17
+// qubits, where a sweep takes microseconds and the compiles dominate a plan's
+// first use, a state of several workgroup tiles keeps them only if some of
+// its passes share a kernel: a larger tile repeats its gate pattern less
+// often (16 qubits, 8 ring layers: no two of 23 passes alike, 25 kernels with
+// the forward from a given state, against 23 kernels for 28 one-wave passes,
+// for a step of 0.686 against 0.889 ms at 6 layers and 64 samples).
+dq_status complete_plan(std::unique_ptr<dq_plan_s> &p) {
+    for (;;) {
+        const dq_status st = build_plan(*p);
+        if (st != DQ_OK) return st;
+        if (p->opt.layout == 0) p.reset(search_layout(p.release()));
+        balance_adjoint(*p);
+        if (p->opt.jit) jit_generate(*p);
+        if (!p->wb_fwd || p->n > 17 || p->n <= 6 + p->Rt_fwd + p->wb_fwd) return DQ_OK;
+        const Program &f = p->has_fold ? p->fwd_fold : p->fwd_full;
+        std::vector<int> kernels(f.jk);
+        kernels.insert(kernels.end(), p->adj.jk.begin(), p->adj.jk.end());
+        std::sort(kernels.begin(), kernels.end());
+        if (std::unique(kernels.begin(), kernels.end()) != kernels.end()) return DQ_OK;
+        std::unique_ptr<dq_plan_s> q(plan_clone_base(*p));
+        q->gates = p->canon;
+        q->one_wave = true;
+        p = std::move(q);
+    }
+}
+
 dq_status ensure_device(dq_plan_s &p, DevData **out) {
     int dev = 0;
     DQ_HIP(hipGetDevice(&dev));
@@ -1207,7 +1595,8 @@ dq_status ensure_device(dq_plan_s &p, DevData **out) {
         for (size_t k = 0; k < p.adj.steps.size(); ++k) {
             if (p.adj.jk.empty() || p.adj.jk[k] < 0) continue;
             const size_t lds = sizeof(double) * 64 * (size_t)std::max<int64_t>(p.adj.steps[k].nls, 1);
-            const int cap = jit_resident(dd.jfn[(size_t)p.adj.jk[k]], lds);
+            const int wb = p.adj.steps[k].wb;   // workgroup tiles hold their accumulators in static LDS
+            const int cap = jit_resident(dd.jfn[(size_t)p.adj.jk[k]], 64 << wb, wb ? 0 : lds);
             if (cap > 0 && (dd.jit_adj_cap == 0 || cap < dd.jit_adj_cap)) dd.jit_adj_cap = cap;
         }
     }
@@ -1332,7 +1721,7 @@ int64_t expval_blocks(int n, int64_t batch) {
 
 int64_t grad_waves(const dq_plan_s &p, int64_t batch) {
     int64_t units;
-    if (p.R_adj > 0) units = int64_t(1) << (p.n - 6 - p.R_adj);      // tiles per sample
+    if (p.R_adj > 0) units = int64_t(1) << (p.n - 6 - p.Rt_adj - p.wb_adj);      // tiles per sample
     else units = std::max<int64_t>(1, (int64_t(1) << p.n) / (256 * 16));
     const int64_t cap = std::max<int64_t>(1, 4096 / batch);
     return std::max<int64_t>(1, std::min(units, cap));
@@ -1415,7 +1804,9 @@ dq_status run_program(dq_plan_s &p, DevData &d, const Program &prog, void *st, v
             a.R = S.R;
             for (int i = 0; i < MAX_TILE_R; ++i) a.rbits[i] = S.rbits[i];
             for (int i = 0; i < 3; ++i) a.lbits[i] = S.lbits[i];
-            for (int i = 0; i < MAX_TILE_R + 3; ++i) a.tbits[i] = S.tbits[i];
+            a.wb = S.wb;
+            for (int i = 0; i < MAX_TILE_W; ++i) a.wbits[i] = S.wbits[i];
+            for (int i = 0; i < MAX_TILE_R + 3 + MAX_TILE_W; ++i) a.tbits[i] = S.tbits[i];
             a.batch = batch;
             a.ops = d.ops + S.op0;
             a.nops = (int32_t)S.nops;
@@ -1535,7 +1926,9 @@ dq_status adjoint_core(dq_plan_s &plan, DevData &d, const dq_obs_s &obs, const D
     int wps = (int)grad_waves(plan, batch);
     if (plan.R_adj > 0) {
         const int resident = d.jit_adj_cap > 0 ? d.jit_adj_cap : tile_adj_capacity(plan.dbl, plan.R_adj);
-        const int cap = std::max<int64_t>(1, resident / batch);
+        // (workgroup tiles: four times as many, as in the forward, since a few
+        // large workgroups per sample would leave the chip's last round uneven)
+        const int cap = std::max<int64_t>(1, (plan.wb_adj ? 4 : 1) * (int64_t)resident / batch);
         wps = std::min(wps, cap);
     }
     void *psi = state;
@@ -1604,11 +1997,8 @@ dq_status ensure_hess_plan(dq_plan_s &p, dq_plan_s **out) {
             }
         q->user_gates = (int64_t)q->gates.size();
         q->canon = q->gates;
-        dq_status st = build_plan(*q);
+        dq_status st = complete_plan(q);
         if (st != DQ_OK) return st;
-        if (q->opt.layout == 0) q.reset(search_layout(q.release()));
-        balance_adjoint(*q);
-        if (q->opt.jit) jit_generate(*q);
         if (q->opt.arith64 && !all_compiled(*q))
             return fail(DQ_ERR_UNSUPPORTED, "arith64: a step of the derived plan is not a compiled tile pass");
         p.hess = std::move(q);
@@ -1854,13 +2244,8 @@ dq_status dq_plan_create(dq_plan *out, int32_t nqubits, const dq_gate *gates, in
             p->hocc.insert(p->hocc.end(), by_param[(size_t)i].begin(), by_param[(size_t)i].end());
         }
     }
-    dq_status st = build_plan(*p);
-    if (st != DQ_OK) {
-        return st;
-    }
-    if (o.layout == 0) p.reset(search_layout(p.release()));
-    balance_adjoint(*p);
-    if (o.jit) jit_generate(*p);
+    dq_status st = complete_plan(p);
+    if (st != DQ_OK) return st;
     if (o.arith64 && !all_compiled(*p))
         return fail(DQ_ERR_UNSUPPORTED, "arith64: a step of this plan is not a compiled tile pass");
     *out = p.release();
@@ -1934,6 +2319,7 @@ dq_status dq_plan_describe(dq_plan plan, char *buf, size_t cap, size_t *needed) 
                          S.lbits[0], S.lbits[1], S.lbits[2]);
                 t += line;
                 for (int i = 0; i < S.R; ++i) t += std::to_string(S.rbits[i]) + (i + 1 < S.R ? "," : "");
+                for (int i = 0; i < S.wb; ++i) t += (i ? "," : " wbits=") + std::to_string(S.wbits[i]);
                 if (k < prog.jk.size() && prog.jk[k] >= 0) t += " kernel=" + plan->jnames[(size_t)prog.jk[k]];
                 t += " ops=";
                 for (int64_t i = 0; i < S.nops; ++i) {
@@ -2347,7 +2733,7 @@ namespace {
 
 bool tile_only(const Program &p, int R) {
     for (const Step &s : p.steps)
-        if (s.kind != ST_TILE || s.R != R) return false;
+        if (s.kind != ST_TILE || s.R != R || s.wb != 0) return false;
     return true;
 }
 

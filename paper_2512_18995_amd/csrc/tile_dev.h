@@ -41,7 +41,7 @@ struct TOp {
     int32_t lslot;     // adjoint: accumulator index inside the pass, -1 none
 };
 
-enum : int32_t { MAX_TILE_R = 6, MAX_LSLOTS = 64 };
+enum : int32_t { MAX_TILE_R = 6, MAX_LSLOTS = 64, MAX_TILE_W = 3 };
 
 struct TileArgs {
     void *st;                  // state [B][2^n]
@@ -49,7 +49,8 @@ struct TileArgs {
     int32_t n, R;
     int32_t rbits[MAX_TILE_R]; // physical bits of the register bits
     int32_t lbits[3];          // physical bits of lane bits 3..5
-    int32_t tbits[MAX_TILE_R + 3];  // lbits and rbits together, ascending
+    int32_t wbits[MAX_TILE_W]; // workgroup tiles: physical bits of the wave bits
+    int32_t tbits[MAX_TILE_R + 3 + MAX_TILE_W];  // lbits, rbits and wbits together, ascending
     int64_t batch;
     const TOp *ops;
     int32_t nops, nlslots;
@@ -59,7 +60,7 @@ struct TileArgs {
     const int32_t *lslot_gslot;// adjoint: global gradient index of each local slot
     int32_t wps, ngrad;
     int32_t nt;                // 1: loads and stores with the non-temporal hint
-    int32_t pad_;
+    int32_t wb;                // wave bits: 2^wb waves of a workgroup share the tile (0: one wave)
 };
 
 
@@ -803,71 +804,93 @@ __device__ __forceinline__ void adj_unit(cx<S> *st, cx<S> *lam, int64_t sbase, i
 // (slots relative to the pass's first matrix), so register selections,
 // swaps and CNOTs between register bits become renamings, and nothing is
 // dispatched at run time.
+//
+// Positions: 0..5 lane bits, 6..6+R-1 register bits, and in workgroup tiles
+// 6+R.. the bits of the wave's index in its workgroup.  `pos` holds this
+// lane's value of every lane and wave bit at its position.  Wave bits, like
+// lane bits, can control and carry diagonal factors; only lane bits can be
+// exchanged across lanes, and only register bits inside a lane.
+template <int NR> constexpr bool is_reg(int q) { return q >= 6 && (1 << (q - 6)) < NR; }
+
 template <typename T, int NS, int NR, int KIND, int Q0, int Q1, int SLOT>
-__device__ __forceinline__ void op_s(cx<T> (&v)[NS][NR], cptr<cx<T>> m, int lane) {
+__device__ __forceinline__ void op_s(cx<T> (&v)[NS][NR], cptr<cx<T>> m, int pos) {
     using V = cx<T>;
+    constexpr bool R0 = is_reg<NR>(Q0), R1 = is_reg<NR>(Q1);
     if constexpr (KIND == TK_1Q) {
         const V m00 = ldc(m, SLOT), m01 = ldc(m, SLOT + 1), m10 = ldc(m, SLOT + 2), m11 = ldc(m, SLOT + 3);
-        if constexpr (Q0 < 6) {
-            const bool hi = (lane >> Q0) & 1;
+        if constexpr (!R0) {
+            static_assert(Q0 < 6, "a wave bit cannot be exchanged");
+            const bool hi = (pos >> Q0) & 1;
             lane_1q<V, NS, NR, Q0>(v, csel(hi, m11, m00), csel(hi, m10, m01));
         } else {
             reg_1q<V, NS, NR, Q0 - 6>(v, m00, m01, m10, m11);
         }
     } else if constexpr (KIND == TK_1QREAL) {
         const T m00 = m[SLOT].x, m01 = m[SLOT + 1].x, m10 = m[SLOT + 2].x, m11 = m[SLOT + 3].x;
-        if constexpr (Q0 < 6) {
-            const bool hi = (lane >> Q0) & 1;
+        if constexpr (!R0) {
+            static_assert(Q0 < 6, "a wave bit cannot be exchanged");
+            const bool hi = (pos >> Q0) & 1;
             lane_1q_real<V, NS, NR, Q0, T>(v, hi ? m11 : m00, hi ? m10 : m01);
         } else {
             reg_1q_real<V, NS, NR, Q0 - 6, T>(v, m00, m01, m10, m11);
         }
     } else if constexpr (KIND == TK_1QRX) {
         const T c = m[SLOT].x, sn = m[SLOT + 1].y;
-        if constexpr (Q0 < 6) lane_1q_rx<V, NS, NR, Q0, T>(v, c, sn);
-        else reg_1q_rx<V, NS, NR, Q0 - 6, T>(v, c, sn);
+        if constexpr (!R0) {
+            static_assert(Q0 < 6, "a wave bit cannot be exchanged");
+            lane_1q_rx<V, NS, NR, Q0, T>(v, c, sn);
+        } else {
+            reg_1q_rx<V, NS, NR, Q0 - 6, T>(v, c, sn);
+        }
     } else if constexpr (KIND == TK_1QDIAG) {
         const V d0 = ldc(m, SLOT), d1 = ldc(m, SLOT + 3);
-        if constexpr (Q0 < 6) {
-            const V d = csel(((lane >> Q0) & 1) != 0, d1, d0);
+        if constexpr (!R0) {
+            const V d = csel(((pos >> Q0) & 1) != 0, d1, d0);
             DQ_SF(NR, { DQ_NS({ v[s_][i] = cmul(d, v[s_][i]); }); });
         } else {
             reg_1q_diag<V, NS, NR, Q0 - 6>(v, d0, d1);
         }
     } else if constexpr (KIND == TK_CNOT) {   // control Q0, target Q1
-        if constexpr (Q1 >= 6 && Q0 >= 6) reg_cnot_rr<V, NS, NR, Q1 - 6, Q0 - 6>(v);
-        else if constexpr (Q1 >= 6) reg_cnot_lc<V, NS, NR, Q1 - 6>(v, (lane >> Q0) & 1);
-        else if constexpr (Q0 >= 6) lane_cnot_rc<V, NS, NR, Q1, Q0 - 6>(v);
-        else lane_cnot_lc<V, NS, NR, Q1>(v, (lane >> Q0) & 1);
-    } else if constexpr (KIND == TK_CZ) {
-        constexpr int A = Q0 < Q1 ? Q0 : Q1, B = Q0 < Q1 ? Q1 : Q0;
-        if constexpr (A >= 6) {
-            reg_cz_rr<V, NS, NR, A - 6, B - 6>(v);
-        } else if constexpr (B >= 6) {
-            reg_sign<V, NS, NR, B - 6, T>(v, ((lane >> A) & 1) ? T(-1) : T(1));
+        if constexpr (R1 && R0) {
+            reg_cnot_rr<V, NS, NR, Q1 - 6, Q0 - 6>(v);
+        } else if constexpr (R1) {
+            reg_cnot_lc<V, NS, NR, Q1 - 6>(v, (pos >> Q0) & 1);
         } else {
-            const T sg = (((lane >> A) & (lane >> B)) & 1) ? T(-1) : T(1);
+            static_assert(Q1 < 6, "a wave bit cannot be exchanged");
+            if constexpr (R0) lane_cnot_rc<V, NS, NR, Q1, Q0 - 6>(v);
+            else lane_cnot_lc<V, NS, NR, Q1>(v, (pos >> Q0) & 1);
+        }
+    } else if constexpr (KIND == TK_CZ) {
+        if constexpr (R0 && R1) {
+            constexpr int A = Q0 < Q1 ? Q0 : Q1, B = Q0 < Q1 ? Q1 : Q0;
+            reg_cz_rr<V, NS, NR, A - 6, B - 6>(v);
+        } else if constexpr (R0 || R1) {
+            constexpr int K = R0 ? Q0 : Q1, L = R0 ? Q1 : Q0;   // the register bit, the other
+            reg_sign<V, NS, NR, K - 6, T>(v, ((pos >> L) & 1) ? T(-1) : T(1));
+        } else {
+            const T sg = (((pos >> Q0) & (pos >> Q1)) & 1) ? T(-1) : T(1);
             DQ_SF(NR, { DQ_NS({ v[s_][i] = V{sg * v[s_][i].x, sg * v[s_][i].y}; }); });
         }
     } else if constexpr (KIND == TK_2QDIAG) {   // diag over (Q0 = msb, Q1)
         const V d0 = ldc(m, SLOT), d1 = ldc(m, SLOT + 5), d2 = ldc(m, SLOT + 10), d3 = ldc(m, SLOT + 15);
-        if constexpr (Q0 >= 6 && Q1 >= 6) {
+        if constexpr (R0 && R1) {
             reg_2qdiag_rr<V, NS, NR, Q0 - 6, Q1 - 6>(v, d0, d1, d2, d3);
-        } else if constexpr (Q1 >= 6) {
-            const bool a = (lane >> Q0) & 1;
+        } else if constexpr (R1) {
+            const bool a = (pos >> Q0) & 1;
             reg_diag2<V, NS, NR, Q1 - 6>(v, csel(a, d2, d0), csel(a, d3, d1));
-        } else if constexpr (Q0 >= 6) {
-            const bool b = (lane >> Q1) & 1;
+        } else if constexpr (R0) {
+            const bool b = (pos >> Q1) & 1;
             reg_diag2<V, NS, NR, Q0 - 6>(v, csel(b, d1, d0), csel(b, d3, d2));
         } else {
-            const bool a = (lane >> Q0) & 1, b = (lane >> Q1) & 1;
+            const bool a = (pos >> Q0) & 1, b = (pos >> Q1) & 1;
             const V d = csel(a, csel(b, d3, d2), csel(b, d1, d0));
             DQ_SF(NR, { DQ_NS({ v[s_][i] = cmul(d, v[s_][i]); }); });
         }
     } else if constexpr (KIND == TK_SWAP) {
         constexpr int A = Q0 < Q1 ? Q0 : Q1, B = Q0 < Q1 ? Q1 : Q0;
+        static_assert((R0 || Q0 < 6) && (R1 || Q1 < 6), "a wave bit cannot be exchanged");
         if constexpr (B < 6) {
-            const bool differ = ((lane >> A) ^ (lane >> B)) & 1;
+            const bool differ = ((pos >> A) ^ (pos >> B)) & 1;
             DQ_SF8(NR, {
                 DQ_NS({
                     const V o = shfl_xor_c(v[s_][i], (1 << A) | (1 << B));
@@ -875,7 +898,7 @@ __device__ __forceinline__ void op_s(cx<T> (&v)[NS][NR], cptr<cx<T>> m, int lane
                 });
             });
         } else if constexpr (A < 6) {
-            lane_reg_swap<V, NS, NR, B - 6, A>(v, lane);
+            lane_reg_swap<V, NS, NR, B - 6, A>(v, pos);
         } else {
             reg_swap<V, NS, NR, A - 6, B - 6>(v);
         }
@@ -974,36 +997,42 @@ template <typename V> __device__ __forceinline__ V cconj(V a) { return V{a.x, -a
 // Im<lambda| P |psi> summed over this lane's registers, for the generator P
 // of a differentiable gate at compile-time positions
 template <typename T, int NR, int GEN, int Q0, int Q1>
-__device__ __forceinline__ T gen_s(const cx<T> (&v)[NR], const cx<T> (&l)[NR], int lane) {
+__device__ __forceinline__ T gen_s(const cx<T> (&v)[NR], const cx<T> (&l)[NR], int pos) {
     using V = cx<T>;
+    constexpr bool R0 = is_reg<NR>(Q0), R1 = is_reg<NR>(Q1);
     if constexpr (GEN == GEN_Z) {
-        if constexpr (Q0 < 6) {
+        if constexpr (!R0) {
             const T s = all_sum<T, V, NR>(v, l);
-            return ((lane >> Q0) & 1) ? -s : s;
+            return ((pos >> Q0) & 1) ? -s : s;
         } else {
             return reg_z_sum<T, V, NR, Q0 - 6>(v, l);
         }
     } else if constexpr (GEN == GEN_ZZ || GEN == GEN_P11) {
-        constexpr int A = Q0 < Q1 ? Q0 : Q1, B = Q0 < Q1 ? Q1 : Q0;
-        if constexpr (A >= 6) {
+        if constexpr (R0 && R1) {
+            constexpr int A = Q0 < Q1 ? Q0 : Q1, B = Q0 < Q1 ? Q1 : Q0;
             if constexpr (GEN == GEN_ZZ) return reg_zz_sum<T, V, NR, A - 6, B - 6>(v, l);
             else return reg_p11_sum<T, V, NR, A - 6, B - 6>(v, l);
-        } else if constexpr (B >= 6) {
+        } else if constexpr (R0 || R1) {
+            constexpr int K = R0 ? Q0 : Q1, L = R0 ? Q1 : Q0;   // the register bit, the other
             if constexpr (GEN == GEN_ZZ) {
-                const T s = reg_z_sum<T, V, NR, B - 6>(v, l);
-                return ((lane >> A) & 1) ? -s : s;
+                const T s = reg_z_sum<T, V, NR, K - 6>(v, l);
+                return ((pos >> L) & 1) ? -s : s;
             } else {
-                const T s = reg_set_sum<T, V, NR, B - 6>(v, l);
-                return ((lane >> A) & 1) ? s : T(0);
+                const T s = reg_set_sum<T, V, NR, K - 6>(v, l);
+                return ((pos >> L) & 1) ? s : T(0);
             }
         } else {
             const T s = all_sum<T, V, NR>(v, l);
-            if constexpr (GEN == GEN_ZZ) return (((lane >> A) ^ (lane >> B)) & 1) ? -s : s;
-            else return (((lane >> A) & (lane >> B)) & 1) ? s : T(0);
+            if constexpr (GEN == GEN_ZZ) return (((pos >> Q0) ^ (pos >> Q1)) & 1) ? -s : s;
+            else return (((pos >> Q0) & (pos >> Q1)) & 1) ? s : T(0);
         }
     } else if constexpr (GEN == GEN_X || GEN == GEN_Y) {
-        if constexpr (Q0 < 6) return lane_xy_sum<T, V, NR, Q0>(v, l, GEN == GEN_Y, (lane >> Q0) & 1);
-        else return reg_xy_sum<T, V, NR, Q0 - 6>(v, l, GEN == GEN_Y);
+        if constexpr (!R0) {
+            static_assert(Q0 < 6, "a wave bit cannot be exchanged");
+            return lane_xy_sum<T, V, NR, Q0>(v, l, GEN == GEN_Y, (pos >> Q0) & 1);
+        } else {
+            return reg_xy_sum<T, V, NR, Q0 - 6>(v, l, GEN == GEN_Y);
+        }
     } else {
         return T(0);
     }
@@ -1038,6 +1067,208 @@ __device__ __forceinline__ void jit_adj(const TileArgs &a, double *acc, Body &&b
     adj_unit<T, R, S>((cx<S> *)a.st, (cx<S> *)a.lam, b << a.n, b << a.n, a.n, a.rbits, a.lbits, a.tbits, a.nlslots, blockIdx.x,
                    a.wps, a.partial + (b * a.wps + blockIdx.x) * (int64_t)a.ngrad, a.lslot_gslot, acc, lane, NT,
                    [&](V (&v)[2][1 << R], double *ac) { body(v, m, lane, ac); });
+}
+
+// ---------------------------------------------------------------- workgroup tiles
+// A compiled pass whose tile is shared by the 2^WB waves of a workgroup:
+// 2^(6+R+WB) amplitudes, two more bits per sweep of the state than one wave's
+// registers hold, so fewer sweeps.  A layout F names the tile bit at every
+// position; tile bit q is physical bit q (q < 3), lbits, rbits, wbits.  The
+// pass loads in the identity layout (lanes on the low physical bits: whole
+// cache lines), runs the operations whose exchanged bits are register bits,
+// moves the tile to another layout through LDS when the next ones need other
+// bits, and stores from a layout whose first lanes are the low bits again.
+// Against one-wave tiles: 28-qubit QFT 29 -> 17 passes, 25.4 -> 16.6 ms;
+// 20-qubit, 16-sample step 22 + 29 -> 17 + 24 passes, 8.2 -> 6.1 ms;
+// 20-qubit Hessian 11.8 -> 9.3 ms; 28 qubits in float64 arithmetic 33 + 44 ->
+// 26 + 30 passes, 114 -> 105 ms.  What bounds a pass: HBM where it has few
+// operations; VALU and LDS beside it where it has many (float64: an exchange
+// of both adjoint states of 2^28 amplitudes costs 0.3 ms of LDS time, which
+// writes 75 and reads 120 bytes a clock and compute unit).
+template <int R> __device__ __forceinline__ int wide_phys(const TileArgs &a, int q) {
+    return q < 3 ? q : (q < 6 ? a.lbits[q - 3] : (q < 6 + R ? a.rbits[q - 6] : a.wbits[q - 6 - R]));
+}
+struct WideId {   // the identity layout
+    static constexpr int at(int p) { return p; }
+};
+// amplitude offset of this lane and wave (register bits zero) in layout F
+template <int R, int WB, typename F> __device__ __forceinline__ int64_t wide_lane_off(const TileArgs &a, int lane) {
+    int64_t o = 0;
+    static_for<0, 6>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        o += int64_t((lane >> p) & 1) << wide_phys<R>(a, F::at(p));
+    });
+    return o;
+}
+template <int R, int WB, typename F> __device__ __forceinline__ int64_t wide_wave_off(const TileArgs &a, int wave) {
+    int64_t o = 0;
+    static_for<0, WB>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        o += int64_t((wave >> p) & 1) << wide_phys<R>(a, F::at(6 + R + p));
+    });
+    return o;
+}
+template <int R, typename F> __device__ __forceinline__ int64_t wide_reg_off(const TileArgs &a, int i) {
+    int64_t o = 0;
+    static_for<0, R>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        if ((i >> p) & 1) o += int64_t(1) << wide_phys<R>(a, F::at(6 + p));
+    });
+    return o;
+}
+
+// Orders LDS accesses between the waves of a workgroup.  Only LDS is
+// fenced: the tile's loads and stores to global memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Moves the tile from one layout to another through LDS, the real parts of
+// every state first, then the imaginary ones (half the LDS, so that two
+// workgroups share a compute unit).  X::w[p] / X::r[p]: the LDS index mask of
+// the bit at position p in the old / new layout; an element's index is the
+// XOR of the masks of its set bits.  The masks are chosen so that the lane
+// bits of both layouts map onto the six lowest index bits one to one: every
+// access of a wave covers 64 consecutive elements, free of bank conflicts.
+// A register's index bits that no lane or wave bit touches are added, so that
+// they become the access's constant offset.
+template <typename T, int NS, int R, int WB, typename X>
+__device__ __forceinline__ void xchg(cx<T> (&v)[NS][1 << R], T *buf, int pos) {
+    constexpr int NR = 1 << R, TB = 6 + R + WB;
+    // the addresses are worth recomputing: hoisted out of the tile loop they
+    // would hold registers through the whole pass
+    asm volatile("" : "+v"(pos));
+    int wa = 0, ra = 0;
+    static_for<0, TB>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        if constexpr (p < 6 || p >= 6 + R) {
+            const int on = -((pos >> p) & 1);
+            wa ^= on & X::w[p];
+            ra ^= on & X::r[p];
+        }
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    auto moves = [&](auto comp) {
+        lds_barrier();   // earlier reads of the buffer are done
+        DQ_SF(NR, {
+            constexpr int c = X::wreg(i), lo = c & X::wlow();
+            DQ_NS({ buf[(wa ^ lo) + (c - lo) + (s_ << TB)] = comp(v[s_][i]); });
+        });
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        DQ_SF(NR, {
+            constexpr int c = X::rreg(i), lo = c & X::rlow();
+            DQ_NS({ comp(v[s_][i]) = buf[(ra ^ lo) + (c - lo) + (s_ << TB)]; });
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    moves([](cx<T> &a) -> T & { return a.x; });
+    moves([](cx<T> &a) -> T & { return a.y; });
+}
+
+// Adds a gradient term to its accumulator: the eight lanes of a half row
+// first (float64), then one LDS entry per half row and wave, [slot][wave][8].
+template <int WB> __device__ __forceinline__ void wide_acc(double *acc, int slot, int lane, int wave, double x) {
+    x += lx<0>(x);
+    x += lx<1>(x);
+    x += lx<2>(x);
+    if ((lane & 7) == 0) acc[(slot << (WB + 3)) + (wave << 3) + (lane >> 3)] += x;
+}
+
+template <typename T, int R, int WB, bool NT, typename S, typename F, typename Body>
+__device__ __forceinline__ void jit_fwd_wide(const TileArgs &a, Body &&body) {
+    using V = cx<T>;
+    constexpr int NR = 1 << R;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int pos = lane | (wave << (6 + R));
+    const int tshift = a.n - 6 - R - WB;
+    const int64_t total = a.batch << tshift;
+    const int64_t tmask = (int64_t(1) << tshift) - 1;
+    const int64_t li = wide_lane_off<R, WB, WideId>(a, lane), lo = wide_lane_off<R, WB, F>(a, lane);
+    const int64_t wi = wide_wave_off<R, WB, WideId>(a, wave), wo = wide_wave_off<R, WB, F>(a, wave);
+    for (int64_t tile = blockIdx.x; tile < total; tile += gridDim.x) {
+        const int64_t b = tile >> tshift;
+        int64_t base = (b << a.n) + tile_base<R + WB>(tile & tmask, a.tbits);
+        const cptr<V> m = to_const((const V *)a.mats + b * a.mstride);
+        V v[1][NR];
+        {
+            const cx<S> *tp = (const cx<S> *)a.st + base + wi;
+            DQ_SF(NR, {
+                const cx<S> *p = tp + wide_reg_off<R, WideId>(a, i) + li;
+                v[0][i] = as_t<T>(NT ? ld_stream(p) : *p);
+            });
+        }
+        // float32 tiles, four waves per SIMD: per-lane factors are recomputed
+        // rather than held in registers from tile to tile
+        if constexpr (sizeof(T) == 4) asm volatile("" : "+v"(pos));
+        body(v, m, pos);
+        asm volatile("" : "+s"(base));
+        {
+            cx<S> *tp = (cx<S> *)a.st + base + wo;
+            DQ_SF(NR, {
+                cx<S> *p = tp + wide_reg_off<R, F>(a, i) + lo;
+                if constexpr (NT) st_stream(p, as_t<S>(v[0][i]));
+                else *p = as_t<S>(v[0][i]);
+            });
+        }
+    }
+}
+
+template <typename T, int R, int WB, bool NT, typename S, typename F, typename Body>
+__device__ __forceinline__ void jit_adj_wide(const TileArgs &a, double *acc, Body &&body) {
+    using V = cx<T>;
+    constexpr int NR = 1 << R;
+    const int64_t b = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int pos = lane | (wave << (6 + R));
+    const cptr<V> m = to_const((const V *)a.mats + b * a.mstride);
+    const int64_t tps = int64_t(1) << (a.n - 6 - R - WB);
+    // this wave's accumulators: no other wave touches them before the end
+    for (int s = 0; s < a.nlslots; ++s)
+        if (lane < 8) acc[(s << (WB + 3)) + (wave << 3) + lane] = 0.0;
+    const int64_t li = wide_lane_off<R, WB, WideId>(a, lane), lo = wide_lane_off<R, WB, F>(a, lane);
+    const int64_t wi = wide_wave_off<R, WB, WideId>(a, wave), wo = wide_wave_off<R, WB, F>(a, wave);
+    V v[2][NR];   // [0] = psi, [1] = lambda
+    for (int64_t t = blockIdx.x; t < tps; t += a.wps) {
+        int64_t base = (b << a.n) + tile_base<R + WB>(t, a.tbits);
+        {
+            const cx<S> *pp = (const cx<S> *)a.st + base + wi, *qp = (const cx<S> *)a.lam + base + wi;
+            DQ_SF(NR, {
+                const int64_t o = wide_reg_off<R, WideId>(a, i) + li;
+                v[0][i] = as_t<T>(NT ? ld_stream(pp + o) : pp[o]);
+                v[1][i] = as_t<T>(NT ? ld_stream(qp + o) : qp[o]);
+            });
+        }
+        if constexpr (sizeof(T) == 4) asm volatile("" : "+v"(pos));   // as in the forward
+        body(v, m, pos, lane, wave);
+        asm volatile("" : "+s"(base));
+        {
+            cx<S> *pp = (cx<S> *)a.st + base + wo, *qp = (cx<S> *)a.lam + base + wo;
+            DQ_SF(NR, {
+                const int64_t o = wide_reg_off<R, F>(a, i) + lo;
+                if constexpr (NT) {
+                    st_stream(pp + o, as_t<S>(v[0][i]));
+                    st_stream(qp + o, as_t<S>(v[1][i]));
+                } else {
+                    pp[o] = as_t<S>(v[0][i]);
+                    qp[o] = as_t<S>(v[1][i]);
+                }
+            });
+        }
+    }
+    lds_barrier();
+    double *row = a.partial + (b * a.wps + blockIdx.x) * (int64_t)a.ngrad;
+    for (int s = wave; s < a.nlslots; s += 1 << WB) {
+        double x = 0.0;
+        for (int k = lane; k < (8 << WB); k += 64) x += acc[(s << (WB + 3)) + k];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        if (lane == 0) row[a.lslot_gslot[s]] = x;
+    }
 }
 
 }  // namespace dq
