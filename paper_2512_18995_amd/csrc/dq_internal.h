@@ -265,12 +265,13 @@ hipError_t launch_probs(int dbl, const void *st, int64_t batch, const ProbArgs &
 hipError_t launch_sample(const double *p, int64_t batch, int32_t nout, const double *u, int32_t shots, int64_t *out,
                          hipStream_t s);
 // Groups [0, ngroups) by the pair kernels (the X-free group 0 by k_zdiag
-// when dt0 < dt1); the one-bit-X terms of the nxs tile sets (host array xs,
-// term lists at device xt) by the tile kernels (complex64 only).
+// when dt0 < dt1; max_group: the most terms any other group holds); the
+// one-bit-X terms of the nxs tile sets (host array xs, term lists at device
+// xt) by the tile kernels (the adjoint seed: complex64 only).
 hipError_t launch_expval(int dbl, const void *st, int32_t n, int64_t batch, const DGroup *groups, int32_t ngroups,
                          const DTerm *terms, int32_t nterms, int32_t nobs, double *partial, int32_t eb, double *out,
                          int32_t dt0, int32_t dt1, double *dpart, const XSet *xs, int32_t nxs, const XTerm *xt,
-                         hipStream_t s);
+                         int32_t max_group, hipStream_t s);
 hipError_t launch_lambda(int dbl, const void *psi, void *lam, int32_t n, int64_t batch, const DGroup *groups,
                          int32_t ngroups, const DTerm *terms, const double *grad_out, int32_t nobs, int32_t dt0, int32_t dt1,
                          const XSet *xs, int32_t nxs, const XTerm *xt, hipStream_t s);

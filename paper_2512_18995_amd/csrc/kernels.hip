@@ -979,7 +979,10 @@ __device__ __forceinline__ void expval_chunk(const cx<T> *p, int64_t N, uint64_t
     __syncthreads();
 }
 
-template <typename T>
+// TM = 4 serves groups of at most four terms (a random Pauli sum has one per X
+// mask) with a quarter of the registers, so that more waves hide the loads'
+// latency: eight groups of one term at 24 qubits 534 -> 148 us.
+template <typename T, int TM>
 __global__ __launch_bounds__(256) void k_expval_part(const cx<T> *st, int n, const DGroup *groups, int g0, int ngroups,
                                                      const DTerm *terms, int nterms, double *partial, int eb) {
     __shared__ double red[4][2 * EXP_TM];
@@ -992,10 +995,10 @@ __global__ __launch_bounds__(256) void k_expval_part(const cx<T> *st, int n, con
     for (int g = g0; g < ngroups; ++g) {
         const uint64_t x = gp[g].xmask;
         const int t0 = gp[g].t0, t1 = gp[g].t1;
-        for (int c0 = t0; c0 < t1; c0 += EXP_TM) {
-            const int nt = (t1 - c0) < EXP_TM ? (t1 - c0) : EXP_TM;
-            if (x == 0) expval_chunk<T, true>(p, N, x, tp, c0, nt, row, eb, red, blockIdx.x);
-            else expval_chunk<T, false>(p, N, x, tp, c0, nt, row, eb, red, blockIdx.x);
+        for (int c0 = t0; c0 < t1; c0 += TM) {
+            const int nt = (t1 - c0) < TM ? (t1 - c0) : TM;
+            if (x == 0) expval_chunk<T, true, TM>(p, N, x, tp, c0, nt, row, eb, red, blockIdx.x);
+            else expval_chunk<T, false, TM>(p, N, x, tp, c0, nt, row, eb, red, blockIdx.x);
         }
     }
 }
@@ -1206,30 +1209,43 @@ __device__ __forceinline__ int xtile_zr(uint64_t z, const XSet &S) {
     for (int r = 0; r < 5; ++r) m |= (int)((z >> S.rb[r]) & 1) << r;
     return m;
 }
-__device__ __forceinline__ C64 bperm_c64(C64 a, int addr) {
-    return C64{__int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(a.x))),
-               __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(a.y)))};
+__device__ __forceinline__ float bperm(float a, int addr) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(a)));
+}
+__device__ __forceinline__ double bperm(double a, int addr) {
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(addr, __double2hiint(a)),
+                            __builtin_amdgcn_ds_bpermute(addr, __double2loint(a)));
+}
+template <typename T> __device__ __forceinline__ cx<T> bperm_c(cx<T> a, int addr) {
+    return cx<T>{bperm(a.x, addr), bperm(a.y, addr)};
 }
 
 // Partial sums S_t = sum_j (-1)^{|j & z_t|} conj(psi_{j^x}) psi_j of the
 // set's terms (as expval_chunk: over the pair members j whose X bit is 0,
 // doubled), one row per block: partial[b][block][t][2].  Per tile and term
-// the wave's sum goes to a per-wave accumulator in LDS.
-__global__ __launch_bounds__(256) void k_xtile_expval(const C64 *st, int n, XSet S, const XTerm *xts, const DTerm *terms,
+// the wave's sum goes to a per-wave accumulator in LDS.  Complex128 tiles hold
+// 128 registers a lane and still win: the 23 transverse-field terms of a
+// 23-qubit state read it four times instead of 23 (846 -> 156 us).
+template <typename T>
+__global__ __launch_bounds__(256) void k_xtile_expval(const cx<T> *st, int n, XSet S, const XTerm *xts, const DTerm *terms,
                                                       int nterms, double *partial, int eb) {
     __shared__ double acc[4][2 * XT_MAX];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t b = blockIdx.y, N = int64_t(1) << n;
-    const C64 *p = st + b * N;
+    const cx<T> *p = st + b * N;
     const int nx = S.x1 - S.x0;
     if (lane < 2 * XT_MAX) acc[wv][lane] = 0.0;
     const int64_t ntiles = N >> 11;
     for (int64_t t = blockIdx.x * 4 + wv; t < ntiles; t += (int64_t)eb * 4) {
         const int64_t base = xtile_base(t, S);
-        C64 v[32];
+        cx<T> v[32];
 #pragma unroll
         for (int k = 0; k < 32; ++k) v[k] = p[base + xtile_reg(k, S) + lane];
         for (int i = 0; i < nx; ++i) {
+            // the pair products do not depend on the term: hoisted out of this
+            // loop they would hold hundreds of registers
+#pragma unroll
+            for (int k = 0; k < 32; ++k) asm volatile("" : "+v"(v[k].x), "+v"(v[k].y));
             const XTerm x = xts[S.x0 + i];
             const uint64_t z = terms[x.t].zmask;
             const int h = x.pos < 6 ? x.pos : S.rb[x.pos - 6];
@@ -1240,13 +1256,13 @@ __global__ __launch_bounds__(256) void k_xtile_expval(const C64 *st, int n, XSet
             if (x.pos < 6) {
                 const int addr = (lane ^ (1 << x.pos)) << 2;
                 const bool mine = !((lane >> x.pos) & 1);
-#pragma unroll
-                for (int k = 0; k < 32; ++k) {
-                    const C64 o = bperm_c64(v[k], addr), a = v[k];
+                // (eight exchanges in flight: all 32 would take their registers)
+                DQ_SF8(32, {
+                    const cx<T> o = bperm_c(v[i], addr), a = v[i];
                     const double c = odd ? (double)(o.x * a.y - o.y * a.x) : (double)(o.x * a.x + o.y * a.y);
-                    const bool neg = (s0 ^ __popc(k & zr)) & 1;
+                    const bool neg = (s0 ^ __popc(i & zr)) & 1;
                     sr += neg ? -c : c;
-                }
+                });
                 if (!mine) sr = 0.0;
             } else {
 #pragma unroll
@@ -1255,7 +1271,7 @@ __global__ __launch_bounds__(256) void k_xtile_expval(const C64 *st, int n, XSet
 #pragma unroll
                     for (int k = 0; k < 32; ++k) {
                         if ((k >> r) & 1) continue;
-                        const C64 a = v[k], o = v[k | (1 << r)];
+                        const cx<T> a = v[k], o = v[k | (1 << r)];
                         const double c = odd ? (double)(o.x * a.y - o.y * a.x) : (double)(o.x * a.x + o.y * a.y);
                         const bool neg = (s0 ^ __popc(k & zr)) & 1;
                         sr += neg ? -c : c;
@@ -1306,7 +1322,7 @@ __global__ __launch_bounds__(256) void k_xtile_lambda(const C64 *psi, C64 *lam, 
                 const int addr = (lane ^ (1 << x.pos)) << 2;
 #pragma unroll
                 for (int k = 0; k < 32; ++k) {
-                    const C64 o = bperm_c64(v[k], addr);
+                    const C64 o = bperm_c(v[k], addr);
                     const bool neg = (s0 ^ __popc(k & zr)) & 1;
                     const float dr = neg ? -wr : wr, di = neg ? -wi : wi;
                     l[k] = C64{l[k].x + (dr * o.x - di * o.y), l[k].y + (dr * o.y + di * o.x)};
@@ -1964,11 +1980,17 @@ hipError_t launch_sample(const double *p, int64_t batch, int32_t nout, const dou
 hipError_t launch_expval(int dbl, const void *st, int32_t n, int64_t batch, const DGroup *groups, int32_t ngroups,
                          const DTerm *terms, int32_t nterms, int32_t nobs, double *partial, int32_t eb, double *out,
                          int32_t dt0, int32_t dt1, double *dpart, const XSet *xs, int32_t nxs, const XTerm *xt,
-                         hipStream_t s) {
-    if (nxs > 0 && (dbl || n < 11)) return hipErrorInvalidValue;
-    for (int k = 0; k < nxs; ++k)
-        hipLaunchKernelGGL(k_xtile_expval, dim3((unsigned)eb, (unsigned)batch), dim3(256), 0, s, (const C64 *)st, n, xs[k],
-                           xt, terms, nterms, partial, eb);
+                         int32_t max_group, hipStream_t s) {
+    if (nxs > 0 && n < 11) return hipErrorInvalidValue;
+    for (int k = 0; k < nxs; ++k) {
+        const dim3 g((unsigned)eb, (unsigned)batch);
+        if (dbl)
+            hipLaunchKernelGGL(k_xtile_expval<double>, g, dim3(256), 0, s, (const C128 *)st, n, xs[k], xt, terms, nterms,
+                               partial, eb);
+        else
+            hipLaunchKernelGGL(k_xtile_expval<float>, g, dim3(256), 0, s, (const C64 *)st, n, xs[k], xt, terms, nterms,
+                               partial, eb);
+    }
     // the X-free group (terms dt0..dt1, group 0) by k_zdiag when dt0 < dt1
     const bool zd = dt0 < dt1;
     const int deb = zd ? zdiag_blocks(n) : 0;
@@ -1984,12 +2006,19 @@ hipError_t launch_expval(int dbl, const void *st, int32_t n, int64_t batch, cons
     const int g0 = zd ? 1 : 0;
     if (ngroups > g0) {
         dim3 g((unsigned)eb, (unsigned)batch);
-        if (dbl)
-            hipLaunchKernelGGL(k_expval_part<double>, g, dim3(256), 0, s, (const C128 *)st, n, groups, g0, ngroups, terms,
-                               nterms, partial, eb);
+        const bool narrow = max_group <= 4;
+        if (dbl && narrow)
+            hipLaunchKernelGGL((k_expval_part<double, 4>), g, dim3(256), 0, s, (const C128 *)st, n, groups, g0, ngroups,
+                               terms, nterms, partial, eb);
+        else if (dbl)
+            hipLaunchKernelGGL((k_expval_part<double, EXP_TM>), g, dim3(256), 0, s, (const C128 *)st, n, groups, g0,
+                               ngroups, terms, nterms, partial, eb);
+        else if (narrow)
+            hipLaunchKernelGGL((k_expval_part<float, 4>), g, dim3(256), 0, s, (const C64 *)st, n, groups, g0, ngroups,
+                               terms, nterms, partial, eb);
         else
-            hipLaunchKernelGGL(k_expval_part<float>, g, dim3(256), 0, s, (const C64 *)st, n, groups, g0, ngroups, terms,
-                               nterms, partial, eb);
+            hipLaunchKernelGGL((k_expval_part<float, EXP_TM>), g, dim3(256), 0, s, (const C64 *)st, n, groups, g0, ngroups,
+                               terms, nterms, partial, eb);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -1692,16 +1692,21 @@ dq_status ensure_obs(dq_obs_s &o, const DGroup **groups, const DTerm **terms) {
 }
 
 // The pair-kernel groups and tile sets of an expectation or adjoint seed on
-// a plan's state: the tile kernels take complex64 states only.
+// a plan's state.  The adjoint seed's tile kernel holds two tiles: complex64
+// states only.
 struct ObsRun {
     int32_t ngroups = 0, nxs = 0;
+    int32_t max_group = 0;   // the most terms of a group that the pair kernels take
     const XSet *xs = nullptr;
     const XTerm *xt = nullptr;
 };
-ObsRun obs_run(const dq_plan_s &p, const dq_obs_s &o, const DTerm *terms) {
+// first: the first group the pair kernels take (1 when the diagonal kernel takes the X-free group)
+ObsRun obs_run(const dq_plan_s &p, const dq_obs_s &o, const DTerm *terms, bool seed, int first) {
     ObsRun r;
-    const bool tiles = !p.dbl && p.n >= 11 && !o.xsets.empty();
+    const bool tiles = !(p.dbl && seed) && p.n >= 11 && !o.xsets.empty();
     r.ngroups = tiles ? o.npair : (int32_t)o.groups.size();
+    for (int32_t g = first; g < r.ngroups; ++g)
+        r.max_group = std::max(r.max_group, o.groups[(size_t)g].t1 - o.groups[(size_t)g].t0);
     if (tiles) {
         r.nxs = (int32_t)o.xsets.size();
         r.xs = o.xsets.data();
@@ -1949,7 +1954,7 @@ dq_status adjoint_core(dq_plan_s &plan, DevData &d, const dq_obs_s &obs, const D
     if (e != hipSuccess) return fail(DQ_ERR_HIP, "prepare: %s", hipGetErrorString(e));
     int32_t dt0, dt1;
     zdiag_range(plan, obs, dt0, dt1);
-    const ObsRun orun = obs_run(plan, obs, t);
+    const ObsRun orun = obs_run(plan, obs, t, true, dt0 < dt1 ? 1 : 0);
     ProfScope pl(plan, DQ_PROF_LAMBDA, 1, 2 * SB, s);
     e = launch_lambda(plan.dbl, psi, lam, plan.n, batch, g, orun.ngroups, t, grad_out, obs.nobs, dt0, dt1, orun.xs,
                       orun.nxs, orun.xt, s);
@@ -2500,12 +2505,13 @@ dq_status dq_expval(dq_plan plan, dq_obs obs, const void *state, int64_t batch, 
     const int eb = (int)expval_blocks(plan->n, batch);
     int32_t dt0, dt1;
     if (!zdiag_range(*plan, *obs, dt0, dt1) || obs->nobs > ZD_MAXOBS) dt0 = dt1 = 0;
-    const ObsRun orun = obs_run(*plan, *obs, t);
+    const ObsRun orun = obs_run(*plan, *obs, t, false, dt0 < dt1 ? 1 : 0);
     ProfScope pe(*plan, DQ_PROF_EXPVAL, 2, state_bytes(*plan, batch) * (double)(orun.ngroups + orun.nxs),
                  (hipStream_t)stream);
     hipError_t e = launch_expval(plan->dbl, state, plan->n, batch, g, orun.ngroups, t, (int32_t)obs->terms.size(),
                                  obs->nobs, (double *)((char *)ws + L.expv), eb, out, dt0, dt1,
-                                 (double *)((char *)ws + L.zdp), orun.xs, orun.nxs, orun.xt, (hipStream_t)stream);
+                                 (double *)((char *)ws + L.zdp), orun.xs, orun.nxs, orun.xt, orun.max_group,
+                                 (hipStream_t)stream);
     pe.done();
     if (e != hipSuccess) return fail(DQ_ERR_HIP, "expval: %s", hipGetErrorString(e));
     return ok();

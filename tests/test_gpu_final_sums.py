@@ -45,3 +45,30 @@ def test_gradient_sums(n, batch, layers, per_sample):
     got, _ = dq.adjoint_grad(plan, obs, st, t64(params), None, t64(w))
     want, _ = oracle.grad_param_shift(c, params, None, observables, w, batch)
     normwise(got.cpu().numpy(), np.asarray(want).reshape(got.shape), 1e-11, 1e-12, "gradients")
+
+
+@pytest.mark.parametrize("dtype,tol", [("c64", 1e-5), ("c128", 1e-12)])
+@pytest.mark.parametrize("n,batch", [(11, 2), (12, 1), (16, 3), (17, 1)])
+def test_one_bit_x_terms(dtype, tol, n, batch):
+    """Terms X_h and Y_h times Z strings on every wire: lane bits, register
+    bits of the first tile set and of the later, padded ones, more than a set
+    holds; beside a group of five terms on one X mask (wide pair kernel)."""
+    rng = np.random.default_rng(80 + n)
+
+    def term(h, letter):
+        zs = {int(w): "Z" for w in rng.choice(n, 3, replace=False)}
+        zs[h] = letter
+        return (float(rng.standard_normal()), "".join(zs.get(w, "I") for w in range(n)))
+
+    one = [term(h, "XY"[h % 2]) for h in range(n)] + [term(0, "X")] * 13
+    pair = [(0.3 * k + 0.1, "X" + "IZ"[k & 1] + "IZ"[(k >> 1) & 1] + "X" + "IZ"[k >> 2] + "I" * (n - 5)) for k in range(5)]
+    observables = [one, pair + W.sum_z(n)]
+    plan, obs = dq.Plan(W.Circuit(n, []), dtype), dq.Observable(n, observables)
+    psi = rng.standard_normal((batch, 1 << n)) + 1j * rng.standard_normal((batch, 1 << n))
+    psi /= np.linalg.norm(psi, axis=1, keepdims=True)
+    got = dq.expval(plan, obs, torch.as_tensor(psi, dtype=plan.state(1, "cpu").dtype, device=DEV)).cpu().numpy()
+    want = np.stack([oracle.expvals(n, psi[b], observables) for b in range(batch)])
+    # the sums of many terms nearly cancel on a random state: the tolerance is
+    # relative to the sum of the coefficients that multiply unit amplitudes
+    scale = np.array([sum(abs(c) for c, _ in o) for o in observables])
+    assert np.all(np.abs(got - want) <= tol * scale), (got, want)
