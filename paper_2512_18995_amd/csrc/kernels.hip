@@ -318,7 +318,33 @@ __global__ __launch_bounds__(256) void k_init_product(cx<T> *st, int n, const cx
 // The same state for n >= 16: a block writes 2^16 consecutive amplitudes whose
 // bits 16.. are fixed (one product per block), bits 8..15 index a 256-entry
 // product table in LDS and bits 0..7 are this thread's (one product per
-// thread), so each amplitude costs one complex multiply.
+// thread), so each amplitude costs one complex multiply.  Call with 256
+// threads; u is filled by them before.
+template <typename T>
+__device__ __forceinline__ void init_product_rows(cx<T> *p, int n, double2 (*u)[2], double2 *tab) {
+    const int t = threadIdx.x;
+    __syncthreads();
+    auto mul = [](double2 a, double2 c) { return double2{a.x * c.x - a.y * c.y, a.x * c.y + a.y * c.x}; };
+    {
+        double2 f{1.0, 0.0};
+        for (int k = 0; k < 8; ++k) f = mul(f, u[8 + k][(t >> k) & 1]);
+        tab[t] = f;
+    }
+    double2 lo{1.0, 0.0};
+    for (int k = 0; k < 8; ++k) lo = mul(lo, u[k][(t >> k) & 1]);
+    __syncthreads();
+    const int64_t nblk = int64_t(1) << (n - 16);
+    for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+        double2 q = lo;
+        for (int k = 16; k < n; ++k) q = mul(q, u[k][(blk >> (k - 16)) & 1]);
+        cx<T> *pb = p + (blk << 16);
+        for (int r = 0; r < 256; ++r) {
+            const double2 a = mul(q, tab[r]);
+            pb[(r << 8) + t] = cx<T>{(T)a.x, (T)a.y};
+        }
+    }
+}
+
 template <typename T, typename M>
 __global__ __launch_bounds__(256) void k_init_product_tab(cx<T> *st, int n, const cx<M> *mats, int64_t mstride,
                                                           const int64_t *fold_off) {
@@ -337,38 +363,21 @@ __global__ __launch_bounds__(256) void k_init_product_tab(cx<T> *st, int n, cons
             u[t][1] = double2{(double)m[2].x, (double)m[2].y};
         }
     }
-    __syncthreads();
-    auto mul = [](double2 a, double2 c) { return double2{a.x * c.x - a.y * c.y, a.x * c.y + a.y * c.x}; };
-    {
-        double2 f{1.0, 0.0};
-        for (int k = 0; k < 8; ++k) f = mul(f, u[8 + k][(t >> k) & 1]);
-        tab[t] = f;
-    }
-    double2 lo{1.0, 0.0};
-    for (int k = 0; k < 8; ++k) lo = mul(lo, u[k][(t >> k) & 1]);
-    __syncthreads();
-    const int64_t nblk = int64_t(1) << (n - 16);
-    cx<T> *p = st + (b << n);
-    for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-        double2 q = lo;
-        for (int k = 16; k < n; ++k) q = mul(q, u[k][(blk >> (k - 16)) & 1]);
-        cx<T> *pb = p + (blk << 16);
-        for (int r = 0; r < 256; ++r) {
-            const double2 a = mul(q, tab[r]);
-            pb[(r << 8) + t] = cx<T>{(T)a.x, (T)a.y};
-        }
-    }
+    init_product_rows<T>(st + (b << n), n, u, tab);
 }
 
 // Uneven batches: every circuit's start state in one launch (blockIdx.y =
-// circuit entry): the folded product state (as k_init_product) or |0..0>.
+// circuit entry): the folded product state or |0..0>, by the products that a
+// single plan forms (as k_init_product, from 16 qubits on as
+// k_init_product_tab: 64 circuits of 12 to 22 qubits 264 -> 109 us).
 template <typename T>
 __global__ __launch_bounds__(256) void k_init_multi(cx<T> *st, const char *ws, const MInit *ents) {
     __shared__ double2 u[64][2];
+    __shared__ double2 tab[256];
     const MInit E = ents[blockIdx.y];
     const int n = E.n;
     const int64_t N = int64_t(1) << n;
-    if (blockIdx.x * (int64_t)blockDim.x >= N) return;   // block-uniform
+    if ((int64_t)blockIdx.x << (n >= 16 ? 16 : 8) >= N) return;   // block-uniform
     if (threadIdx.x < n) {
         const int64_t off = E.has_fold ? E.fold[threadIdx.x] : -1;
         if (off < 0) {
@@ -380,8 +389,12 @@ __global__ __launch_bounds__(256) void k_init_multi(cx<T> *st, const char *ws, c
             u[threadIdx.x][1] = double2{(double)m[2].x, (double)m[2].y};
         }
     }
-    __syncthreads();
     cx<T> *p = st + E.st_off;
+    if (n >= 16) {
+        init_product_rows<T>(p, n, u, tab);
+        return;
+    }
+    __syncthreads();
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < N; j += (int64_t)gridDim.x * blockDim.x) {
         double2 acc{1.0, 0.0};
         for (int k = 0; k < n; ++k) {
