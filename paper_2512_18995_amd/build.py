@@ -30,6 +30,8 @@ UNITS = [
     ("tiles.hip", "tiles_fwd_c128", ["-DDQ_TILES_F64"]),
     ("tiles.hip", "tiles_adj_c64", ["-DDQ_TILES_ADJ"]),
     ("tiles.hip", "tiles_adj_c128", ["-DDQ_TILES_ADJ", "-DDQ_TILES_F64"]),
+    ("wg.hip", "wg_fwd", []),
+    ("wg.hip", "wg_adj", ["-DDQ_WG_ADJ"]),
 ]
 ARCH = "gfx950"
 ROCM_LIB = "/opt/rocm/lib"
@@ -69,7 +71,7 @@ RESOURCE_REMARK = "-Rpass-analysis=kernel-resource-usage"
 # kernels that stream the state through registers: none of them may keep
 # registers in scratch memory (such tile kernels ran for minutes on states
 # of a few thousand amplitudes)
-NO_SCRATCH = ("k_tile_", "k_dense_", "k_gate", "k_cnot", "k_cz", "k_init", "k_expval", "k_zdiag", "k_xtile", "k_lambda")
+NO_SCRATCH = ("k_tile_", "k_wg_", "k_dense_", "k_gate", "k_cnot", "k_cz", "k_init", "k_expval", "k_zdiag", "k_xtile", "k_lambda")
 
 
 def parse_resources(text: str) -> dict:

@@ -71,6 +71,48 @@ struct MultiEntry {
     int32_t tbits[MAX_TILE_R + 3];
 };
 
+// ---------------------------------------------------------------- interpreted workgroup tiles
+// One operation of a pass at the positions it has when it runs (0..5 lane
+// bits, 6..6+R-1 register bits, 6+R.. wave bits):
+//   WG_REAL / WG_RX / WG_1Q   one gate per register bit b: slot a[2b] (-1
+//                             none), gradient slot a[2b+1] (-1 none)
+//   WG_DIAG                   gates a[0] .. a[0]+a[1]-1 of the diagonal table
+//                             (at most 64); a[2] != 0: some carry a gradient
+//   WG_CNOT                   control position a[0], target register bit a[1]
+//   WG_CZ                     positions a[0], a[1]
+//   WG_2QDIAG                 positions a[0], a[1], slot a[2], generator a[3],
+//                             gradient slot a[4] (swaps are three CNOTs)
+//   WG_XCHG                   layout exchange a[0] of the exchange table
+enum : int32_t { WG_REAL = 0, WG_RX, WG_1Q, WG_DIAG, WG_CNOT, WG_CZ, WG_2QDIAG, WG_XCHG };
+enum : int32_t { WG_WAVE_BITS = 2, WG_MAX_T = 13, WG_MAX_LSLOTS = 64, WG_MAX_RUN = 64 };
+struct WgOp {
+    int32_t kind;
+    int32_t a[11];
+};
+struct WgDiag {
+    int32_t q, slot, lslot, pad;
+};
+struct WgX {               // LDS byte masks per position of the old and new layout, and the lanes' parts
+    int32_t w[16], r[16];
+    int32_t lw[64], lr[64];
+};
+struct WgPass {
+    int32_t n, R, nops, nls, nt;
+    int32_t touch;                           // read the two-qubit diagonal gates' matrices ahead
+    int32_t pin[WG_MAX_T], pout[WG_MAX_T];   // physical bit of every position, on load and on store
+    int32_t tbits[WG_MAX_T];                 // the tile's physical bits above 2, ascending
+    const WgOp *ops;
+    const WgDiag *diag;
+    const WgX *xs;
+    const int32_t *lsg;                      // gradient slot -> global gradient index
+};
+// the same for one circuit of an uneven batch (offsets as in MultiEntry)
+struct WgEntry {
+    int64_t st_off, lam_off, mats_off, part_off, unit_begin;
+    int32_t wps, ngrad;
+    WgPass pass;
+};
+
 // The per-circuit steps of an uneven batch that surround the tile passes,
 // one launch each over all circuits: matrix preparation, start states,
 // expectations, the adjoint seed and the final gradient sums.  Offsets:
@@ -183,6 +225,13 @@ hipError_t tile_adj_multi_f32(int R, void *st, void *ws, const MultiEntry *e, in
                               hipStream_t s);
 hipError_t tile_adj_multi_f64(int R, void *st, void *ws, const MultiEntry *e, int32_t n, int64_t units, size_t lds,
                               hipStream_t s);
+// interpreted workgroup passes (wg.hip; complex64)
+hipError_t wg_fwd(const WgPass &a, void *st, const void *mats, int64_t mstride, int64_t batch, hipStream_t s);
+hipError_t wg_adj(const WgPass &a, void *st, void *lam, const void *mats, int64_t mstride, double *partial, int32_t wps,
+                  int32_t ngrad, int64_t batch, hipStream_t s);
+hipError_t wg_fwd_multi(int R, void *st, void *ws, const WgEntry *e, int32_t n, int64_t units, hipStream_t s);
+hipError_t wg_adj_multi(int R, void *st, void *ws, const WgEntry *e, int32_t n, int64_t units, int32_t max_nls,
+                        hipStream_t s);
 // passes compiled at plan time (jit.cpp): jit_key names the kernel of a
 // source body (a hash that also covers tile_dev.h and the compiler options);
 // jit_load returns, for the current device, the kernels of the given names

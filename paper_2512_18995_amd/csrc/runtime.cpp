@@ -147,6 +147,9 @@ struct Step {
     int wb = 0;                     // wave bits of a workgroup tile (compiled passes only)
     int32_t wbits[MAX_TILE_W] = {0};
     int32_t tbits[MAX_TILE_R + 3 + MAX_TILE_W] = {0};
+    int64_t wg0 = 0, nwg = 0;       // interpreted workgroup tile: into plan.wgops
+    int32_t wgtouch = 0;                       // 1: eight or more two-qubit diagonal gates
+    int32_t pout[WG_MAX_T] = {0};   // and its physical bit of every position on store
     int64_t op0 = 0, nops = 0;      // into plan.ops
     int64_t ls0 = 0, nls = 0;       // into plan.lsg
     int k = 0;
@@ -177,6 +180,9 @@ struct DevData {
     DBlock *blocks = nullptr;
     int32_t *factors = nullptr;
     TOp *ops = nullptr;
+    WgOp *wgops = nullptr;
+    WgDiag *wgdiag = nullptr;
+    WgX *wgx = nullptr;
     int32_t *lsg = nullptr;
     int64_t *fold = nullptr;
     int64_t *poff = nullptr, *doff = nullptr;
@@ -203,6 +209,9 @@ struct dq_plan_s {
     int64_t block = 0;                  // complex elements per sample's matrix block
     std::vector<TOp> ops;
     std::vector<int32_t> lsg;
+    std::vector<WgOp> wgops;            // interpreted workgroup tiles
+    std::vector<WgDiag> wgdiag;
+    std::vector<WgX> wgx;
     Program fwd_full, fwd_fold, adj;
     bool has_fold = false;
     std::vector<std::string> jnames, jsrcs;   // compiled passes: kernel names and sources
@@ -319,11 +328,16 @@ struct Planner {
     // compiled-kernel size limit and run interpreted, and the interpreted
     // kernel with 64 registers per lane keeps its tile in scratch memory
     int max_ops = 0;        // 0: no limit
+    int max_lslots = 32;    // gradient terms per pass (their accumulators share the LDS)
     bool fusing = false;    // one-qubit gates on a wire fold into one operation (forward)
     int cap;                // tile bits above physical bit 2
     explicit Planner(dq_plan_s &pl, bool adj)
         : p(pl), adjoint(adj), R(adj ? pl.Rt_adj : pl.Rt_fwd), W(adj ? pl.wb_adj : pl.wb_fwd), cap(R + 3 + W) {
         if (p.opt.jit && R > 0) max_ops = (int)(kJitMaxWork >> R);
+        // workgroup tiles: the scheduler searches over a pass's operations
+        // (and a small tile's compiled pass would become very long)
+        if (W > 0) max_ops = p.opt.jit ? std::min(max_ops, 128) : 256;
+        if (W > 0 && !p.opt.jit) max_lslots = WG_MAX_LSLOTS;
         const int64_t state_bytes = (int64_t)(p.dbl ? 16 : 8) << p.n;
         // auto: bits 3 and 4 in both directions.  Pinning bit 3 alone frees
         // one more bit for gates (fewer adjoint passes), but its 128-byte
@@ -385,7 +399,7 @@ struct Planner {
                 Q |= 1ull << q[i];
                 if (q[i] >= 3) need |= 1ull << q[i];
             }
-            if ((Q & blocked) || !tile_ok(g) || (diff(g) && lslots >= 32) || popc(S | need) > cap) {
+            if ((Q & blocked) || !tile_ok(g) || (diff(g) && lslots >= max_lslots) || popc(S | need) > cap) {
                 blocked |= Q;
                 continue;
             }
@@ -800,19 +814,24 @@ int default_R(const dq_plan_s &p) {
     return R < 0 ? 0 : R;
 }
 
-// Tiles shared by the waves of a workgroup: compiled passes whose tile shape
-// the caller leaves to the planner.  Measured against one-wave tiles (forward
-// + adjoint of the ring ansatz, complex64, 6 layers unless stated): 10 to 14
+// Tiles shared by the waves of a workgroup: plans whose tile shape the caller
+// leaves to the planner, unless they run interpreted complex128 passes (23
+// qubits, forward only: 20 one-wave passes of 77 us against 11 workgroup
+// passes of 152).  Measured against one-wave tiles, compiled passes (forward +
+// adjoint of the ring ansatz, complex64, 6 layers unless stated): 10 to 14
 // qubits, where most of the state is one tile, 0.159 -> 0.112 ms (10) to
 // 0.393 -> 0.338 ms (14), 200 samples 0.179 -> 0.131 to 0.695 -> 0.520 ms;
 // 15 to 17 qubits, 64 samples, 0.656 -> 0.483, 0.889 -> 0.686, 1.376 ->
 // 1.226 ms; 31 qubits, 4 layers, 417 -> 343 ms (float64 arithmetic 506 -> 498).
 // Registers of 32 qubits and more keep one-wave tiles: there the gain is 3 %
 // (734 -> 712 ms, float64 arithmetic 1026 -> 985 ms).  Below 10 qubits a
-// tile would leave fewer than two register bits per wave.
+// tile would leave fewer than two register bits per wave.  Interpreted passes
+// (same step): 10 qubits 0.224 -> 0.103 ms, 13 qubits 0.50 -> 0.29 ms and with
+// 100 samples 0.55 -> 0.19 ms, 16 qubits 0.62 -> 0.41 ms, 22 qubits 1.53 ->
+// 0.70 ms; six circuits of 12 to 14 qubits 0.45 -> 0.35 ms.
 bool workgroup_tiles(const dq_plan_s &p) {
-    return p.opt.fusion && p.opt.jit && p.opt.tile_bits == 0 && !p.opt.dense_fuse && !p.one_wave && p.n >= 10 &&
-           p.n <= 31;
+    return p.opt.fusion && p.opt.tile_bits == 0 && !p.opt.dense_fuse && !p.one_wave && p.n >= 10 &&
+           p.n <= 31 && (p.opt.jit || !p.dbl);
 }
 // Two bits more than the one-wave tile with R register bits.  float32
 // arithmetic: eight waves with one register bit less each, so that four waves
@@ -820,9 +839,14 @@ bool workgroup_tiles(const dq_plan_s &p) {
 // four waves and two per SIMD).  float64 arithmetic: four waves, because an
 // exchange through LDS moves twice the bytes and fewer register bits need
 // more of them (28 qubits, 8 layers: 101 ms against 115.6 with eight waves).
+// Interpreted passes hold up to twice the registers of a compiled one beside
+// their tile: four waves, two per SIMD (64 uneven circuits: 18.0 ms against
+// 20.9 with eight waves of one register bit less; a state of one tile, 12
+// qubits and 64 samples, takes 291 us a training step with either, and eight
+// waves for those alone would give circuits of mixed sizes a launch per shape).
 void workgroup_shape(const dq_plan_s &p, int R, int &Rt, int &wb) {
     const int T = std::min(p.n, 6 + R + 2);
-    wb = std::min<int>(p.mdbl ? 2 : 3, T - 8);
+    wb = p.opt.jit ? std::min<int>(p.mdbl ? 2 : 3, T - 8) : (int)WG_WAVE_BITS;
     Rt = T - 6 - wb;
 }
 
@@ -1018,13 +1042,15 @@ struct WideSchedule {
 // runs whose exchanged bits are register bits; diagonal operations and
 // controls may sit anywhere.  When none is left that can, either the tile
 // moves to the layout whose register bits let most of the following
-// operations run, or operations on lane bits run as cross-lane exchanges; a
+// operations run (the exchange performing the CNOTs that are ready), or
+// operations on lane bits run as cross-lane exchanges; a
 // small search over these choices minimises the cost, in VALU instructions
 // per amplitude and state: an exchange through LDS costs what about `kx`
 // instructions do (its LDS time and barriers), a cross-lane operation what its
 // lane moves add to the register form.
 struct WideScheduler {
     int R, W, TB, hold, dbl;
+    bool lane_ops;          // operations may run across lanes
     const std::vector<TOp> &ops;
     struct State {
         std::vector<char> done;
@@ -1032,6 +1058,10 @@ struct WideScheduler {
         double cost = 0;
         std::vector<TOp> items;
         std::vector<std::vector<int>> lay;   // layouts (position -> tile bit), the first is the identity
+        // CNOTs (control, target tile bits) that the next exchange performs,
+        // and those of the exchanges so far
+        std::vector<std::pair<int, int>> pending;
+        std::vector<std::vector<std::pair<int, int>>> pre;
         int left = 0;
     };
     State best;
@@ -1064,9 +1094,10 @@ struct WideScheduler {
         return o.kind == TK_SWAP ? 2 * c : c;
     }
     bool runs(const State &s, const TOp &o, bool lanes) const {
+        if (o.kind == TK_CNOT && !lane_ops && !lanes) return false;   // (interpreted: left to the next exchange)
         for (uint64_t mv = moved(o); mv; mv &= mv - 1) {
             const int q = s.at[__builtin_ctzll(mv)];
-            if (!reg(q) && !(lanes && q < 6)) return false;
+            if (!reg(q) && !(lanes && lane_ops && q < 6)) return false;
         }
         return true;
     }
@@ -1079,7 +1110,7 @@ struct WideScheduler {
                 continue;
             }
             TOp o = ops[k];
-            if (lanes) s.cost += lane_cost(s, o);
+            if (lanes) s.cost += lane_ops ? lane_cost(s, o) : (o.kind == TK_CNOT ? 12.0 : 0.0);
             const bool two = bits(o) != (1ull << o.q0);
             o.q0 = s.at[o.q0];
             if (two) o.q1 = s.at[o.q1];
@@ -1102,6 +1133,27 @@ struct WideScheduler {
             S = need;
         }
         return S;
+    }
+    // CNOTs and swaps permute amplitudes linearly in their index, so an
+    // exchange performs any that are ready, wherever their bits are, by other
+    // index masks alone
+    void absorb(State &s) const {
+        uint64_t blocked = 0;
+        for (size_t k = 0; k < ops.size(); ++k) {
+            if (s.done[k]) continue;
+            const TOp &o = ops[k];
+            if ((bits(o) & blocked) || (o.kind != TK_CNOT && o.kind != TK_SWAP)) {
+                blocked |= bits(o);
+                continue;
+            }
+            s.pending.push_back({o.q0, o.q1});
+            if (o.kind == TK_SWAP) {
+                s.pending.push_back({o.q1, o.q0});
+                s.pending.push_back({o.q0, o.q1});
+            }
+            s.done[k] = 1;
+            --s.left;
+        }
     }
     void exchange(State &s, uint64_t S) const {
         const std::vector<int> &from = s.lay.back();
@@ -1130,6 +1182,8 @@ struct WideScheduler {
         x.q0 = (int)s.lay.size() - 1;
         x.lslot = -1;
         s.items.push_back(x);
+        s.pre.push_back(std::move(s.pending));
+        s.pending.clear();
         s.lay.push_back(to);
         for (int p = 0; p < TB; ++p) s.at[to[p]] = p;
         s.cost += dbl ? 36.0 : 18.0;
@@ -1139,40 +1193,75 @@ struct WideScheduler {
             if (s.at[p] != p) return false;
         return true;
     }
+    void finish(State &s) {
+        if (!s.pending.empty() || !storable(s)) exchange(s, 0);
+        if (!found || s.cost < best.cost) {
+            best = std::move(s);
+            found = true;
+        }
+    }
     void search(State s) {
         emit(s, false);
-        if (s.left == 0) {
-            if (!storable(s)) exchange(s, 0);
-            if (!found || s.cost < best.cost) {
-                best = std::move(s);
-                found = true;
-            }
-            return;
-        }
+        if (s.left == 0) return finish(s);
         if ((found && s.cost >= best.cost) || ++nodes > 2000) {
             if (found) return;
         }
-        const uint64_t a = next_regs(s, false), b = next_regs(s, true);
-        {
+        for (int spare_low = 0; spare_low < 2; ++spare_low) {
             State t = s;
-            exchange(t, a);
+            absorb(t);
+            if (t.left == 0) {
+                finish(t);
+                break;
+            }
+            const uint64_t S = next_regs(t, spare_low != 0);
+            if (spare_low && (S == 0 || S == next_regs(t, false))) break;
+            exchange(t, S);
             search(std::move(t));
         }
-        if (b && b != a) {
-            State t = s;
-            exchange(t, b);
-            search(std::move(t));
-        }
-        State t = s;
+        State t = s;   // what can run in this layout across lanes; interpreted: register CNOTs
         emit(t, true);
         if (t.left < s.left) search(std::move(t));
     }
 };
 
-WideSchedule wide_schedule(const dq_plan_s &p, const Step &S, bool adj) {
-    (void)adj;
-    const std::vector<TOp> ops(p.ops.begin() + S.op0, p.ops.begin() + S.op0 + S.nops);
-    WideScheduler W{S.R, S.wb, 6 + S.R + S.wb, 3, p.mdbl, ops, {}, false, 0};
+// The schedule of a pass: the execution order, the layouts, and per exchange
+// the index masks of every position before and after it.
+struct WidePlan {
+    WideScheduler::State best;
+    int TB = 0;
+    std::vector<std::pair<std::vector<int>, std::vector<int>>> masks;   // old, new layout
+};
+
+int gf2_rank(std::vector<int> v) {
+    int r = 0;
+    for (int bit = 0; bit < 31; ++bit) {
+        size_t k = (size_t)r;
+        while (k < v.size() && !((v[k] >> bit) & 1)) ++k;
+        if (k == v.size()) continue;
+        std::swap(v[(size_t)r], v[k]);
+        for (size_t j = 0; j < v.size(); ++j)
+            if (j != (size_t)r && ((v[j] >> bit) & 1)) v[j] ^= v[(size_t)r];
+        ++r;
+    }
+    return r;
+}
+
+WidePlan plan_wide(const dq_plan_s &p, const Step &S, bool lane_ops) {
+    std::vector<TOp> ops;
+    for (int64_t k = 0; k < S.nops; ++k) {
+        const TOp &o = p.ops[(size_t)(S.op0 + k)];
+        if (o.kind != TK_SWAP || lane_ops) {
+            ops.push_back(o);
+            continue;
+        }
+        for (int t = 0; t < 3; ++t) {   // without lane moves a swap is three CNOTs
+            TOp c = o;
+            c.kind = TK_CNOT;
+            if (t == 1) std::swap(c.q0, c.q1);
+            ops.push_back(c);
+        }
+    }
+    WideScheduler W{S.R, S.wb, 6 + S.R + S.wb, 3, p.mdbl, lane_ops, ops, {}, false, 0};
     while (W.hold < 6 && S.lbits[W.hold - 3] == W.hold) ++W.hold;   // lanes that continue the low bits
     W.hold = std::min(W.hold, 5);
     WideScheduler::State s;
@@ -1182,21 +1271,18 @@ WideSchedule wide_schedule(const dq_plan_s &p, const Step &S, bool adj) {
     for (int q = 0; q < W.TB; ++q) s.at[q] = id[q] = q;
     s.lay.push_back(id);
     W.search(s);
-    const WideScheduler::State &r = W.best;
-    WideSchedule out;
-    out.items = r.items;
-    out.exchanges = (int)r.lay.size() - 1;
-    auto list = [](const std::vector<int> &v) {
-        std::string t;
-        for (size_t i = 0; i < v.size(); ++i) t += (i ? ", " : "") + std::to_string(v[i]);
-        return t;
-    };
-    for (int k = 0; k < out.exchanges; ++k) {
-        // index masks of the tile bits: the common lane bits and the new
-        // layout's other lane bits are index bits 0..5; each of the old
-        // layout's other lane bits is XORed onto one of the latter beside an
-        // index bit of its own
-        const std::vector<int> &F = r.lay[(size_t)k], &G = r.lay[(size_t)k + 1];
+    WidePlan out;
+    out.best = std::move(W.best);
+    out.TB = W.TB;
+    for (size_t k = 0; k + 1 < out.best.lay.size(); ++k) {
+        // Index masks of the tile bits.  Reading in the new layout G: the
+        // common lane bits and G's other lane bits are index bits 0..5; each
+        // of the old layout's other lane bits is XORed onto one of the latter
+        // beside an index bit of its own.  The old layout F writes where the
+        // exchange's CNOTs move its elements: their columns are folded into
+        // the masks, last CNOT first.
+        const std::vector<int> &F = out.best.lay[k], &G = out.best.lay[k + 1];
+        const auto &cnots = out.best.pre[k];
         std::vector<int> M(W.TB, 0), f, g;
         int lowb = 0, high = 6;
         for (int i = 0; i < 6; ++i) {
@@ -1212,11 +1298,144 @@ WideSchedule wide_schedule(const dq_plan_s &p, const Step &S, bool adj) {
         for (int q = 0; q < W.TB; ++q)
             if (M[q] == 0) M[q] = 1 << high++;
         if (lowb != 6 || high != W.TB) throw std::runtime_error("workgroup tile: exchange masks do not cover the tile");
+        auto written = [&](const std::vector<int> &m) {
+            std::vector<int> w(m);
+            for (size_t c = cnots.size(); c-- > 0;) w[cnots[c].first] ^= w[cnots[c].second];
+            return w;
+        };
+        // every access of a wave covers 64 different low index values, when
+        // the six lanes' masks are independent there; CNOTs between lane and
+        // other bits can break that for the writes: then the low parts of
+        // the masks are redrawn (a fixed sequence) until both sides hold and
+        // the map stays one to one
+        auto lanes_ok = [&](const std::vector<int> &m, const std::vector<int> &L) {
+            std::vector<int> v;
+            for (int i = 0; i < 6; ++i) v.push_back(m[L[i]] & 63);
+            return gf2_rank(v) == 6;
+        };
+        uint32_t seed = 12345;
+        std::vector<int> N(M);
+        for (int tries = 0; tries < 4000 && !(gf2_rank(N) == W.TB && lanes_ok(N, G) && lanes_ok(written(N), F)); ++tries)
+            for (int q = 0; q < W.TB; ++q) {
+                seed = seed * 1664525u + 1013904223u;
+                N[q] = (M[q] & ~63) | (int)((seed >> 16) & 63);
+            }
+        if (gf2_rank(N) != W.TB) N = M;   // (correct in any case; conflicts only cost time)
+        const std::vector<int> wr = written(N);
         std::vector<int> w(W.TB), rd(W.TB);
         for (int q = 0; q < W.TB; ++q) {
-            w[q] = M[F[q]];
-            rd[q] = M[G[q]];
+            w[q] = wr[F[q]];
+            rd[q] = N[G[q]];
         }
+        out.masks.push_back({w, rd});
+    }
+    return out;
+}
+
+// Interpreted workgroup tiles: the schedule as device tables.  Between two
+// exchanges, gates of one kind on different register bits join one block and
+// one-qubit diagonal gates one run, past gates on other bits.
+void wg_generate(dq_plan_s &p) {
+    if (p.opt.jit) return;
+    auto gen = [&](Program &prog) {
+        for (Step &S : prog.steps) {
+            if (S.kind != ST_TILE || S.wb == 0) continue;
+            const WidePlan wp = plan_wide(p, S, false);
+            const int x0 = (int)p.wgx.size(), amp = sizeof(float);
+            for (const auto &m : wp.masks) {
+                WgX X{};
+                for (int q = 0; q < wp.TB; ++q) {
+                    X.w[q] = m.first[(size_t)q] * amp;
+                    X.r[q] = m.second[(size_t)q] * amp;
+                }
+                for (int l = 0; l < 64; ++l)
+                    for (int q = 0; q < 6; ++q)
+                        if ((l >> q) & 1) {
+                            X.lw[l] ^= X.w[q];
+                            X.lr[l] ^= X.r[q];
+                        }
+                p.wgx.push_back(X);
+            }
+            auto phys = [&](int q) { return q < 3 ? q : (q < 6 ? S.lbits[q - 3] : (q < 6 + S.R ? S.rbits[q - 6] : S.wbits[q - 6 - S.R])); };
+            for (int q = 0; q < wp.TB; ++q) S.pout[q] = phys(wp.best.lay.back()[(size_t)q]);
+            S.wg0 = (int64_t)p.wgops.size();
+            const std::vector<TOp> &it = wp.best.items;
+            std::vector<char> done(it.size(), 0);
+            for (size_t i = 0; i < it.size(); ++i) {
+                if (done[i]) continue;
+                const TOp &o = it[i];
+                WgOp w{};
+                if (o.kind == TK_XCHG) {
+                    w.kind = WG_XCHG;
+                    w.a[0] = x0 + o.q0;
+                    p.wgops.push_back(w);
+                    continue;
+                }
+                const bool block = o.kind == TK_1QREAL || o.kind == TK_1QRX || o.kind == TK_1Q;
+                if (!block && o.kind != TK_1QDIAG) {
+                    w.kind = o.kind == TK_CNOT ? WG_CNOT : (o.kind == TK_CZ ? WG_CZ : WG_2QDIAG);
+                    w.a[0] = o.q0;
+                    w.a[1] = o.kind == TK_CNOT ? o.q1 - 6 : o.q1;
+                    w.a[2] = o.slot;
+                    w.a[3] = o.gen;
+                    w.a[4] = o.lslot;
+                    p.wgops.push_back(w);
+                    continue;
+                }
+                if (block) {
+                    w.kind = o.kind == TK_1QREAL ? WG_REAL : (o.kind == TK_1QRX ? WG_RX : WG_1Q);
+                    for (int b = 0; b < 5; ++b) w.a[2 * b] = w.a[2 * b + 1] = -1;
+                } else {
+                    w.kind = WG_DIAG;
+                    w.a[0] = (int)p.wgdiag.size();
+                }
+                uint64_t blocked = 0;
+                for (size_t j = i; j < it.size() && it[j].kind != TK_XCHG; ++j) {
+                    if (done[j]) continue;
+                    const TOp &g = it[j];
+                    const uint64_t b = WideScheduler::bits(g);
+                    bool take = g.kind == o.kind && !(b & blocked);
+                    if (take && block) take = w.a[2 * (g.q0 - 6)] < 0;
+                    if (take && !block) take = w.a[1] < WG_MAX_RUN;
+                    if (!take) {
+                        blocked |= b;
+                        continue;
+                    }
+                    done[j] = 1;
+                    if (block) {
+                        w.a[2 * (g.q0 - 6)] = g.slot;
+                        w.a[2 * (g.q0 - 6) + 1] = g.lslot;
+                    } else {
+                        p.wgdiag.push_back(WgDiag{g.q0, g.slot, g.lslot, 0});
+                        w.a[1] += 1;
+                        w.a[2] |= g.lslot >= 0;
+                    }
+                }
+                p.wgops.push_back(w);
+            }
+            S.nwg = (int64_t)p.wgops.size() - S.wg0;
+            const auto from = p.wgops.begin() + S.wg0;
+            S.wgtouch = std::count_if(from, p.wgops.end(), [](const WgOp &w) { return w.kind == WG_2QDIAG; }) >= 8;
+        }
+    };
+    gen(p.fwd_full);
+    if (p.has_fold) gen(p.fwd_fold);
+    gen(p.adj);
+}
+
+WideSchedule wide_schedule(const dq_plan_s &p, const Step &S) {
+    const WidePlan W = plan_wide(p, S, true);
+    const WideScheduler::State &r = W.best;
+    WideSchedule out;
+    out.items = r.items;
+    out.exchanges = (int)W.masks.size();
+    auto list = [](const std::vector<int> &v) {
+        std::string t;
+        for (size_t i = 0; i < v.size(); ++i) t += (i ? ", " : "") + std::to_string(v[i]);
+        return t;
+    };
+    for (int k = 0; k < out.exchanges; ++k) {
+        const std::vector<int> &w = W.masks[(size_t)k].first, &rd = W.masks[(size_t)k].second;
         const std::string n = std::to_string(W.TB), R = std::to_string(S.R);
         // index bits that a lane or wave bit touches
         auto low = [&](const char *name, const std::vector<int> &m) {
@@ -1259,7 +1478,7 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
     // the operations at their positions: a workgroup tile's pass interleaves
     // them with exchanges of its layout
     WideSchedule sch;
-    if (S.wb) sch = wide_schedule(p, S, adj);
+    if (S.wb) sch = wide_schedule(p, S);
     else sch.items.assign(p.ops.begin() + S.op0, p.ops.begin() + S.op0 + S.nops);
     auto is_reg = [&](int q) { return q >= 6 && q < 6 + R; };
     if (S.wb) b += sch.layouts;
@@ -1526,7 +1745,8 @@ dq_status complete_plan(std::unique_ptr<dq_plan_s> &p) {
         if (p->opt.layout == 0) p.reset(search_layout(p.release()));
         balance_adjoint(*p);
         if (p->opt.jit) jit_generate(*p);
-        if (!p->wb_fwd || p->n > 17 || p->n <= 6 + p->Rt_fwd + p->wb_fwd) return DQ_OK;
+        else wg_generate(*p);
+        if (!p->opt.jit || !p->wb_fwd || p->n > 17 || p->n <= 6 + p->Rt_fwd + p->wb_fwd) return DQ_OK;
         const Program &f = p->has_fold ? p->fwd_fold : p->fwd_full;
         std::vector<int> kernels(f.jk);
         kernels.insert(kernels.end(), p->adj.jk.begin(), p->adj.jk.end());
@@ -1551,7 +1771,8 @@ dq_status ensure_device(dq_plan_s &p, DevData **out) {
     std::vector<char> blob;
     const size_t o_b = put(blob, p.blocks), o_fa = put(blob, p.factors);
     const size_t o_g = put(blob, p.gates), o_f = put(blob, p.fixed), o_s = put(blob, p.slots),
-                 o_o = put(blob, p.ops), o_l = put(blob, p.lsg), o_fo = put(blob, p.fold_off),
+                 o_o = put(blob, p.ops), o_l = put(blob, p.lsg), o_wo = put(blob, p.wgops),
+                 o_wd = put(blob, p.wgdiag), o_wx = put(blob, p.wgx), o_fo = put(blob, p.fold_off),
                  o_po = put(blob, p.poff), o_pg = put(blob, p.pg), o_pf = put(blob, p.pf),
                  o_do = put(blob, p.doff), o_dg = put(blob, p.dg), o_df = put(blob, p.df),
                  o_op = put(blob, p.occ_param), o_os = put(blob, p.occ_scale), o_ho = put(blob, p.hoff),
@@ -1573,6 +1794,9 @@ dq_status ensure_device(dq_plan_s &p, DevData **out) {
     dd.factors = (int32_t *)(b + o_fa);
     dd.ops = (TOp *)(b + o_o);
     dd.lsg = (int32_t *)(b + o_l);
+    dd.wgops = (WgOp *)(b + o_wo);
+    dd.wgdiag = (WgDiag *)(b + o_wd);
+    dd.wgx = (WgX *)(b + o_wx);
     dd.fold = (int64_t *)(b + o_fo);
     dd.poff = (int64_t *)(b + o_po);
     dd.pg = (int32_t *)(b + o_pg);
@@ -1773,6 +1997,26 @@ WsLayout layout(const dq_plan_s &p, const dq_obs_s *o, int64_t batch, int per_sa
 }
 
 // ---------------------------------------------------------------- execution
+WgPass make_wg_pass(const dq_plan_s &p, const DevData &d, const Step &S, bool nt) {
+    WgPass a{};
+    a.n = p.n;
+    a.R = S.R;
+    a.nops = (int32_t)S.nwg;
+    a.nls = (int32_t)S.nls;
+    a.nt = nt ? 1 : 0;
+    a.touch = S.wgtouch;
+    for (int q = 0; q < 6 + S.R + S.wb; ++q) {
+        a.pin[q] = q < 3 ? q : (q < 6 ? S.lbits[q - 3] : (q < 6 + S.R ? S.rbits[q - 6] : S.wbits[q - 6 - S.R]));
+        a.pout[q] = S.pout[q];
+    }
+    for (int k = 0; k < 3 + S.R + S.wb; ++k) a.tbits[k] = S.tbits[k];
+    a.ops = d.wgops + S.wg0;
+    a.diag = d.wgdiag;
+    a.xs = d.wgx;
+    a.lsg = d.lsg + S.ls0;
+    return a;
+}
+
 dq_status run_program(dq_plan_s &p, DevData &d, const Program &prog, void *st, void *lam, int64_t batch,
                       const void *mats, int64_t mstride, double *partial, int wps, hipStream_t s, bool timed = true) {
     const double SB = state_bytes(p, batch);
@@ -1827,6 +2071,12 @@ dq_status run_program(dq_plan_s &p, DevData &d, const Program &prog, void *st, v
             if (!prog.jk.empty() && prog.jk[si] >= 0 && (size_t)prog.jk[si] < d.jfn.size()) {
                 a.mats = (const char *)mats + prog.js0[si] * (p.mdbl ? 16 : 8);
                 e = jit_launch(d.jfn[prog.jk[si]], p.jnames[prog.jk[si]], a, lam != nullptr, s);
+            } else if (S.wb) {
+                const WgPass g = make_wg_pass(p, d, S, a.nt != 0);
+                if (lam)
+                    e = wg_adj(g, st, lam, mats, mstride, partial, wps, p.ngrad, batch, s);
+                else
+                    e = wg_fwd(g, st, mats, mstride, batch, s);
             } else {
                 e = lam ? launch_tile_adj(p.dbl, a, s) : launch_tile_fwd(p.dbl, a, s);
             }
@@ -1930,7 +2180,9 @@ dq_status adjoint_core(dq_plan_s &plan, DevData &d, const dq_obs_s &obs, const D
     // round of waves covers every tile
     int wps = (int)grad_waves(plan, batch);
     if (plan.R_adj > 0) {
-        const int resident = d.jit_adj_cap > 0 ? d.jit_adj_cap : tile_adj_capacity(plan.dbl, plan.R_adj);
+        // (interpreted workgroup tiles: two workgroups on each of 256 compute units)
+        const int resident = d.jit_adj_cap > 0 ? d.jit_adj_cap
+                                               : (plan.wb_adj ? 512 : tile_adj_capacity(plan.dbl, plan.R_adj));
         // (workgroup tiles: four times as many, as in the forward, since a few
         // large workgroups per sample would leave the chip's last round uneven)
         const int cap = std::max<int64_t>(1, (plan.wb_adj ? 4 : 1) * (int64_t)resident / batch);
@@ -2719,10 +2971,22 @@ struct dq_multi_s {
     std::vector<int32_t> adj_maxnls;
     std::vector<int32_t> wps;                          // adjoint waves per circuit
     std::vector<int> bc;                               // the batched circuits, in order
+    // batched workgroup tiles: one launch per depth and register-bit count,
+    // over consecutive entries (circuit, step)
+    struct WgLaunch {
+        int R;
+        int64_t first, count, units;
+        int32_t max_nls;
+    };
+    bool wg = false;
+    std::vector<WgEntry> went;
+    std::vector<std::pair<int, const Step *>> wref;
+    std::vector<WgLaunch> wfwd, wadj;
     std::mutex mu;
     struct Dev {
         void *blob = nullptr;
         std::vector<MultiEntry *> fwd, adj;
+        WgEntry *went = nullptr;
         // the per-circuit steps around the tile passes, one launch each
         MPrep *prep_fwd = nullptr, *prep_adj = nullptr;
         MInit *init = nullptr;
@@ -2741,6 +3005,15 @@ bool tile_only(const Program &p, int R) {
     for (const Step &s : p.steps)
         if (s.kind != ST_TILE || s.R != R || s.wb != 0) return false;
     return true;
+}
+bool wg_only(const Program &p) {
+    for (const Step &s : p.steps)
+        if (s.kind != ST_TILE || s.wb == 0) return false;
+    return true;
+}
+// interpreted workgroup tiles in both directions
+bool wg_plan(const dq_plan_s &p) {
+    return !p.opt.jit && p.wb_fwd > 0 && p.wb_adj > 0;
 }
 
 MultiEntry make_entry(const Step &S, int n) {
@@ -2788,6 +3061,11 @@ dq_status ensure_multi(dq_multi_s &m, dq_multi_s::Dev **out) {
     for (size_t k = 0; k < m.adj.size(); ++k) {
         astart.push_back(all.size());
         resolve(m.adj[k], m.adj_c[k]);
+    }
+    std::vector<WgEntry> went(m.went);
+    for (size_t i = 0; i < went.size(); ++i) {
+        const int c = m.wref[i].first;
+        went[i].pass = make_wg_pass(*m.plans[c], m.plans[c]->dev[dev], *m.wref[i].second, went[i].pass.nt != 0);
     }
     // the batched circuits' per-circuit steps, resolved for this device
     dq_multi_s::Dev D;
@@ -2860,7 +3138,7 @@ dq_status ensure_multi(dq_multi_s &m, dq_multi_s::Dev **out) {
     }
     std::vector<char> blob;
     const size_t o_all = put(blob, all), o_pf = put(blob, pf), o_pa = put(blob, pa), o_in = put(blob, in),
-                 o_ex = put(blob, ex), o_gr = put(blob, gr);
+                 o_ex = put(blob, ex), o_gr = put(blob, gr), o_we = put(blob, went);
     DQ_HIP(hipMalloc(&D.blob, std::max<size_t>(blob.size(), 1)));
     hipError_t e = hipMemcpy(D.blob, blob.data(), blob.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -2870,6 +3148,7 @@ dq_status ensure_multi(dq_multi_s &m, dq_multi_s::Dev **out) {
     char *bb = (char *)D.blob;
     for (size_t k : fstart) D.fwd.push_back((MultiEntry *)(bb + o_all) + k);
     for (size_t k : astart) D.adj.push_back((MultiEntry *)(bb + o_all) + k);
+    D.went = (WgEntry *)(bb + o_we);
     D.prep_fwd = (MPrep *)(bb + o_pf);
     D.prep_adj = (MPrep *)(bb + o_pa);
     D.init = (MInit *)(bb + o_in);
@@ -2909,6 +3188,7 @@ dq_status dq_multi_create(dq_multi *out, const dq_plan *plans, const dq_obs *obs
         if (p->R_fwd > 0 && !p->opt.arith64) {
             m->R_fwd = p->R_fwd;
             m->R_adj = p->R_adj;
+            m->wg = wg_plan(*p);
             break;
         }
     const size_t amp = m->dbl ? 16 : 8;
@@ -2927,6 +3207,10 @@ dq_status dq_multi_create(dq_multi *out, const dq_plan *plans, const dq_obs *obs
         const Program &f = p->has_fold ? p->fwd_fold : p->fwd_full;
         // batched: pure tile programs of the common shape, for which the
         // multi-circuit kernels exist; the rest take the single-plan path
+        if (m->wg) {   // workgroup tiles batch whatever their register bits
+            m->batched.push_back(wg_plan(*p) && wg_only(f) && wg_only(p->adj));
+            continue;
+        }
         m->batched.push_back(!p->opt.arith64 && p->R_fwd > 0 && p->R_fwd == m->R_fwd && p->R_adj == m->R_adj &&
                              tile_only(f, m->R_fwd) &&
                              tile_only(p->adj, m->R_adj) && multi_fwd_has(m->dbl, m->R_fwd) &&
@@ -2942,7 +3226,38 @@ dq_status dq_multi_create(dq_multi *out, const dq_plan *plans, const dq_obs *obs
     }
     // depth tables
     const double tot_bytes = (double)m->st_total * (double)amp;   // all circuits' states
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < 2 && m->wg; ++pass) {
+        size_t depth = 0;
+        auto prog_of = [&](int c) -> const Program & {
+            const dq_plan_s &p = *m->plans[c];
+            return pass ? p.adj : (p.has_fold ? p.fwd_fold : p.fwd_full);
+        };
+        for (int c : m->bc) depth = std::max(depth, prog_of(c).steps.size());
+        for (size_t d = 0; d < depth; ++d)
+            for (int R = MAX_TILE_R; R >= 1; --R) {
+                dq_multi_s::WgLaunch L{R, (int64_t)m->went.size(), 0, 0, 0};
+                for (int c : m->bc) {
+                    if (prog_of(c).steps.size() <= d || prog_of(c).steps[d].R != R) continue;
+                    const Step &S = prog_of(c).steps[d];
+                    WgEntry E{};
+                    E.st_off = m->st_off[c];
+                    E.mats_off = (int64_t)(m->ws_off[c] + m->lay[c].mats);
+                    E.lam_off = (int64_t)(m->ws_off[c] + m->lay[c].lam);
+                    E.part_off = (int64_t)(m->ws_off[c] + m->lay[c].part);
+                    E.ngrad = m->plans[c]->ngrad;
+                    E.wps = pass ? m->wps[c] : 1;
+                    E.unit_begin = L.units;
+                    E.pass.nt = tot_bytes * (pass ? 2 : 1) > kStreamBytes ? 1 : 0;
+                    L.units += pass ? E.wps : int64_t(1) << (m->plans[c]->n - 6 - S.R - S.wb);
+                    L.max_nls = std::max<int32_t>(L.max_nls, (int32_t)S.nls);
+                    ++L.count;
+                    m->went.push_back(E);
+                    m->wref.push_back({c, &S});
+                }
+                if (L.count) (pass ? m->wadj : m->wfwd).push_back(L);
+            }
+    }
+    for (int pass = 0; pass < 2 && !m->wg; ++pass) {
         auto &tab = pass ? m->adj : m->fwd;
         auto &tabc = pass ? m->adj_c : m->fwd_c;
         auto &units = pass ? m->adj_units : m->fwd_units;
@@ -3050,6 +3365,10 @@ dq_status dq_multi_apply(dq_multi m, void *states, const double *params, void *w
         e = launch_tile_fwd_multi(m->dbl, m->R_fwd, states, ws, D->fwd[k], (int32_t)m->fwd[k].size(), m->fwd_units[k], s);
         if (e != hipSuccess) return fail(DQ_ERR_HIP, "multi tile pass: %s", hipGetErrorString(e));
     }
+    for (const auto &L : m->wfwd) {
+        e = wg_fwd_multi(L.R, states, ws, D->went + L.first, (int32_t)L.count, L.units, s);
+        if (e != hipSuccess) return fail(DQ_ERR_HIP, "multi tile pass: %s", hipGetErrorString(e));
+    }
     return ok();
 } DQ_CATCH
 
@@ -3100,6 +3419,10 @@ dq_status dq_multi_adjoint_grad(dq_multi m, void *states, const double *params, 
     for (size_t k = 0; k < m->adj.size(); ++k) {
         e = launch_tile_adj_multi(m->dbl, m->R_adj, states, ws, D->adj[k], (int32_t)m->adj[k].size(), m->adj_units[k],
                                   m->adj_maxnls[k], s);
+        if (e != hipSuccess) return fail(DQ_ERR_HIP, "multi adjoint pass: %s", hipGetErrorString(e));
+    }
+    for (const auto &L : m->wadj) {
+        e = wg_adj_multi(L.R, states, ws, D->went + L.first, (int32_t)L.count, L.units, L.max_nls, s);
         if (e != hipSuccess) return fail(DQ_ERR_HIP, "multi adjoint pass: %s", hipGetErrorString(e));
     }
     e = launch_grad_final_multi(ws, D->grad, nb, D->grad_total, grad_params, s);

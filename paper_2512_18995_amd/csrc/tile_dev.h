@@ -1080,8 +1080,9 @@ __device__ __forceinline__ void jit_adj(const TileArgs &a, double *acc, Body &&b
 // bits, and stores from a layout whose first lanes are the low bits again.
 // Against one-wave tiles: 28-qubit QFT 29 -> 17 passes, 25.4 -> 16.6 ms;
 // 20-qubit, 16-sample step 22 + 29 -> 17 + 24 passes, 8.2 -> 6.1 ms;
-// 20-qubit Hessian 11.8 -> 9.3 ms; 28 qubits in float64 arithmetic 33 + 44 ->
-// 26 + 30 passes, 114 -> 105 ms.  What bounds a pass: HBM where it has few
+// 20-qubit Hessian 11.8 -> 9.3 ms, and 8.8 with CNOTs and swaps folded into the
+// exchanges' index masks; 28 qubits in float64 arithmetic 33 + 44 -> 26 + 30
+// passes, 114 -> 105 and 94 ms.  What bounds a pass: HBM where it has few
 // operations; VALU and LDS beside it where it has many (float64: an exchange
 // of both adjoint states of 2^28 amplitudes costs 0.3 ms of LDS time, which
 // writes 75 and reads 120 bytes a clock and compute unit).
