@@ -1722,8 +1722,14 @@ dq_plan_s *search_layout(dq_plan_s *p_in) {
                 }
             q->entry_gates = k;
             q->layout_swaps = k;
-            if (build_plan(*q) == DQ_OK && plan_cost(*q) < best) {
-                best = plan_cost(*q);
+            if (build_plan(*q) != DQ_OK) continue;
+            const double cost = plan_cost(*q);
+            // workgroup tiles: as many passes as the canonical order is enough
+            // (the relabelled order keeps ring neighbours off the pinned bits; a
+            // tie is worth -3 to 1 %: 24 qubits, 4 ring layers, 1.88 -> 1.94 ms,
+            // 26 qubits in float64 arithmetic, 2 layers, 5.67 -> 5.61 ms)
+            if (cost < best || (cost == best && !chosen && q->wb_fwd > 0)) {
+                best = cost;
                 chosen = std::move(q);
             }
         }
