@@ -1727,8 +1727,14 @@ dq_plan_s *search_layout(dq_plan_s *p_in) {
             // workgroup tiles: as many passes as the canonical order is enough
             // (the relabelled order keeps ring neighbours off the pinned bits; a
             // tie is worth -3 to 1 %: 24 qubits, 4 ring layers, 1.88 -> 1.94 ms,
-            // 26 qubits in float64 arithmetic, 2 layers, 5.67 -> 5.61 ms)
-            if (cost < best || (cost == best && !chosen && q->wb_fwd > 0)) {
+            // 26 qubits in float64 arithmetic, 2 layers, 5.67 -> 5.61 ms), unless a
+            // forward from a given state, which the relabelling swaps enter, or the
+            // adjoint then has more of them (the Fourier transform of 28 qubits:
+            // 16.4 ms against 18.1)
+            const bool tie = cost == best && !chosen && q->wb_fwd > 0 &&
+                             q->fwd_full.steps.size() <= p->fwd_full.steps.size() &&
+                             q->adj.steps.size() <= p->adj.steps.size();
+            if (cost < best || tie) {
                 best = cost;
                 chosen = std::move(q);
             }
