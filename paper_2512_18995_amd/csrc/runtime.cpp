@@ -15,6 +15,7 @@
 #include <optional>
 #include <stdexcept>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/dq.h"
@@ -1043,38 +1044,82 @@ struct WideSchedule {
 // controls may sit anywhere.  When none is left that can, either the tile
 // moves to the layout whose register bits let most of the following
 // operations run (the exchange performing the CNOTs that are ready), or
-// operations on lane bits run as cross-lane exchanges; a
-// small search over these choices minimises the cost, in VALU instructions
-// per amplitude and state: an exchange through LDS costs what about `kx`
-// instructions do (its LDS time and barriers), a cross-lane operation what its
-// lane moves add to the register form.
+// operations on lane bits run as cross-lane exchanges.  A beam search over
+// these choices minimises the cost in VALU instructions per amplitude and
+// state: an exchange through LDS costs what about 18 instructions do (its LDS
+// time and barriers; 36 in float64), a cross-lane operation what its lane moves
+// add to the register form.  After every choice the kBeam states go on that are
+// cheapest with a share of an estimate of what is to come: one exchange per R
+// bits that its operations have to find in registers.  Taken in full it prefers
+// states that got far, and finds few exchanges; a share of 0.3 finds the
+// schedules in which CNOTs run between registers instead.  The better of both
+// is kept.
+//
+// A state is the set of operations to come and the layout; the schedule itself
+// is written when the best path is run again.  A scan over the operations ends
+// where every tile bit is taken, so a state costs the operations near the
+// front, not those of the whole pass.  Depth-first over up to 2000 states, each
+// with a schedule of its own, scanned over all operations and not kept for the
+// passes that repeat, the search found schedules 0.1 (interpreted passes) to
+// 0.9 % (compiled ones) dearer and took most of a plan's time: 64 plans of 12
+// to 22 qubits 5.9 s against 0.40 now (0.25 for one-wave tiles), 12 qubits and
+// 600 random gates 230 against 12 ms.
 struct WideScheduler {
-    int R, W, TB, hold, dbl;
+    enum : int { kBeam = 8 };
+    int R, TB, hold, dbl;
     bool lane_ops;          // operations may run across lanes
     const std::vector<TOp> &ops;
+    std::vector<uint32_t> touch, moved;   // per operation: its tile bits, and those it exchanges
     struct State {
-        std::vector<char> done;
-        int at[32];     // tile bit -> position
+        std::vector<uint64_t> todo;     // operations to come, one bit each
+        size_t word = 0;                // words of todo before this one are zero
+        int8_t at[16], lay[16];         // tile bit -> position, position -> tile bit
         double cost = 0;
-        std::vector<TOp> items;
+        int left = 0, needs = 0;        // operations to come, and the bits they have to find in registers
+        int choice = -1;                // the last choice, in `choices`
+    };
+    // one choice of the search: an exchange to register bits `regs`, the
+    // operations that run across lanes, or the exchange that ends the pass
+    enum Kind { EXCHANGE, LANES, END };
+    struct Choice {
+        Kind kind;
+        uint32_t regs;
+        int before;
+    };
+    std::vector<Choice> choices;
+    int best = -1;          // the last choice of the cheapest schedule so far
+    double best_cost = 0;
+    bool found = false;
+    // the schedule, written while the best path is run again
+    struct Item {
+        int op;      // into ops, -1: an exchange
+        int q0, q1;  // positions, or the number of the exchange
+    };
+    struct Record {
+        std::vector<Item> items;
         std::vector<std::vector<int>> lay;   // layouts (position -> tile bit), the first is the identity
         // CNOTs (control, target tile bits) that the next exchange performs,
         // and those of the exchanges so far
         std::vector<std::pair<int, int>> pending;
         std::vector<std::vector<std::pair<int, int>>> pre;
-        int left = 0;
     };
-    State best;
-    bool found = false;
-    int nodes = 0;
+    Record *rec = nullptr;
 
+    WideScheduler(int R_, int W_, int hold_, int dbl_, bool lane_ops_, const std::vector<TOp> &ops_)
+        : R(R_), TB(6 + R_ + W_), hold(hold_), dbl(dbl_), lane_ops(lane_ops_), ops(ops_) {
+        for (const TOp &o : ops) {
+            touch.push_back((uint32_t)bits(o));
+            moved.push_back((uint32_t)exchanged(o));
+        }
+    }
     bool reg(int p) const { return p >= 6 && p < 6 + R; }
+    double exchange_cost() const { return dbl ? 36.0 : 18.0; }
     static uint64_t bits(const TOp &o) {
         const bool two = o.kind == TK_CNOT || o.kind == TK_CZ || o.kind == TK_2QDIAG || o.kind == TK_SWAP;
         return (1ull << o.q0) | (two ? 1ull << o.q1 : 0);
     }
     // tile bits an operation exchanges
-    static uint64_t moved(const TOp &o) {
+    static uint64_t exchanged(const TOp &o) {
         switch (o.kind) {
         case TK_1QDIAG: case TK_CZ: case TK_2QDIAG: return 0;
         case TK_CNOT: return 1ull << o.q1;
@@ -1082,155 +1127,229 @@ struct WideScheduler {
         default: return 1ull << o.q0;
         }
     }
+    // Visits the operations to come in order; one that shares a bit with an
+    // earlier one that f refused is refused as well.
+    template <typename F> void scan(State &s, F &&f) const {
+        const uint32_t all = (1u << TB) - 1;
+        uint32_t blocked = 0;
+        while (s.word < s.todo.size() && !s.todo[s.word]) ++s.word;
+        for (size_t w = s.word; w < s.todo.size(); ++w)
+            for (uint64_t m = s.todo[w]; m; m &= m - 1) {
+                const size_t k = w * 64 + (size_t)__builtin_ctzll(m);
+                if (!(touch[k] & blocked) && f(k)) continue;
+                blocked |= touch[k];
+                if (blocked == all) return;
+            }
+    }
+    // an exchange performs CNOTs and swaps wherever their bits are
+    int needs(size_t k) const { return ops[k].kind == TK_CNOT || ops[k].kind == TK_SWAP ? 0 : __builtin_popcount(moved[k]); }
+    void take(State &s, size_t k) const {
+        s.todo[k >> 6] &= ~(1ull << (k & 63));
+        --s.left;
+        s.needs -= needs(k);
+    }
     // what the lane moves of an operation on a lane position add (32-bit words moved)
-    double lane_cost(const State &s, const TOp &o) const {
+    double lane_cost(const State &s, size_t k) const {
         static const int word[6] = {1, 1, 2, 2, 4, 4};
         double c = 0;
-        const int wide = dbl ? 4 : 2;
-        for (uint64_t mv = moved(o); mv; mv &= mv - 1) {
-            const int q = s.at[__builtin_ctzll(mv)];
-            if (q < 6) c += word[q] * wide + (o.kind == TK_CNOT || o.kind == TK_SWAP ? wide : 0);
+        const int wide = dbl ? 4 : 2, kind = ops[k].kind;
+        for (uint32_t mv = moved[k]; mv; mv &= mv - 1) {
+            const int q = s.at[__builtin_ctz(mv)];
+            if (q < 6) c += word[q] * wide + (kind == TK_CNOT || kind == TK_SWAP ? wide : 0);
         }
-        return o.kind == TK_SWAP ? 2 * c : c;
+        return kind == TK_SWAP ? 2 * c : c;
     }
-    bool runs(const State &s, const TOp &o, bool lanes) const {
-        if (o.kind == TK_CNOT && !lane_ops && !lanes) return false;   // (interpreted: left to the next exchange)
-        for (uint64_t mv = moved(o); mv; mv &= mv - 1) {
-            const int q = s.at[__builtin_ctzll(mv)];
+    bool runs(const State &s, size_t k, bool lanes) const {
+        if (ops[k].kind == TK_CNOT && !lane_ops && !lanes) return false;   // (interpreted: left to the next exchange)
+        for (uint32_t mv = moved[k]; mv; mv &= mv - 1) {
+            const int q = s.at[__builtin_ctz(mv)];
             if (!reg(q) && !(lanes && lane_ops && q < 6)) return false;
         }
         return true;
     }
     void emit(State &s, bool lanes) const {
-        uint64_t blocked = 0;
-        for (size_t k = 0; k < ops.size(); ++k) {
-            if (s.done[k]) continue;
-            if ((bits(ops[k]) & blocked) || !runs(s, ops[k], lanes)) {
-                blocked |= bits(ops[k]);
-                continue;
+        scan(s, [&](size_t k) {
+            if (!runs(s, k, lanes)) return false;
+            if (lanes) s.cost += lane_ops ? lane_cost(s, k) : (ops[k].kind == TK_CNOT ? 12.0 : 0.0);
+            if (rec) {
+                const TOp &o = ops[k];
+                const bool two = touch[k] != (1u << o.q0);
+                rec->items.push_back({(int)k, s.at[o.q0], two ? s.at[o.q1] : o.q1});
             }
-            TOp o = ops[k];
-            if (lanes) s.cost += lane_ops ? lane_cost(s, o) : (o.kind == TK_CNOT ? 12.0 : 0.0);
-            const bool two = bits(o) != (1ull << o.q0);
-            o.q0 = s.at[o.q0];
-            if (two) o.q1 = s.at[o.q1];
-            s.items.push_back(o);
-            s.done[k] = 1;
-            --s.left;
-        }
+            take(s, k);
+            return true;
+        });
     }
     // the register bits that let most of the next operations run
-    uint64_t next_regs(const State &s, bool spare_low) const {
-        uint64_t S = 0, blocked = 0;
-        const uint64_t low = (1ull << hold) - 1;
-        for (size_t k = 0; k < ops.size(); ++k) {
-            if (s.done[k]) continue;
-            const uint64_t need = S | moved(ops[k]);
-            if ((bits(ops[k]) & blocked) || __builtin_popcountll(need) > R || (spare_low && (moved(ops[k]) & low))) {
-                blocked |= bits(ops[k]);
-                continue;
-            }
+    uint32_t next_regs(State &s, bool spare_low) const {
+        uint32_t S = 0;
+        const uint32_t low = (1u << hold) - 1;
+        scan(s, [&](size_t k) {
+            const uint32_t need = S | moved[k];
+            if (__builtin_popcount(need) > R || (spare_low && (moved[k] & low))) return false;
             S = need;
-        }
+            return true;
+        });
         return S;
     }
     // CNOTs and swaps permute amplitudes linearly in their index, so an
     // exchange performs any that are ready, wherever their bits are, by other
     // index masks alone
-    void absorb(State &s) const {
-        uint64_t blocked = 0;
-        for (size_t k = 0; k < ops.size(); ++k) {
-            if (s.done[k]) continue;
+    bool absorb(State &s) const {
+        bool any = false;
+        scan(s, [&](size_t k) {
             const TOp &o = ops[k];
-            if ((bits(o) & blocked) || (o.kind != TK_CNOT && o.kind != TK_SWAP)) {
-                blocked |= bits(o);
-                continue;
+            if (o.kind != TK_CNOT && o.kind != TK_SWAP) return false;
+            if (rec) {
+                rec->pending.push_back({o.q0, o.q1});
+                if (o.kind == TK_SWAP) {
+                    rec->pending.push_back({o.q1, o.q0});
+                    rec->pending.push_back({o.q0, o.q1});
+                }
             }
-            s.pending.push_back({o.q0, o.q1});
-            if (o.kind == TK_SWAP) {
-                s.pending.push_back({o.q1, o.q0});
-                s.pending.push_back({o.q0, o.q1});
-            }
-            s.done[k] = 1;
-            --s.left;
-        }
+            take(s, k);
+            any = true;
+            return true;
+        });
+        return any;
     }
-    void exchange(State &s, uint64_t S) const {
-        const std::vector<int> &from = s.lay.back();
+    void exchange(State &s, uint32_t S) const {
         // pad with the bits that are in registers now, then any but the low ones
-        for (int p = 6; p < 6 + R && __builtin_popcountll(S) < R; ++p)
-            if (from[p] >= hold) S |= 1ull << from[p];
-        for (int b = TB - 1; b >= 0 && __builtin_popcountll(S) < R; --b) S |= 1ull << b;
-        std::vector<int> to(TB, -1);
-        uint64_t placed = 0;
+        for (int p = 6; p < 6 + R && __builtin_popcount(S) < R; ++p)
+            if (s.lay[p] >= hold) S |= 1u << s.lay[p];
+        for (int b = TB - 1; b >= 0 && __builtin_popcount(S) < R; --b) S |= 1u << b;
+        int8_t to[16];
+        std::fill(to, to + 16, (int8_t)-1);
+        uint32_t placed = 0;
         auto put = [&](int p, int b) {
-            to[p] = b;
-            placed |= 1ull << b;
+            to[p] = (int8_t)b;
+            placed |= 1u << b;
         };
         for (int p = 0; p < 6; ++p)
             if (!((S >> p) & 1)) put(p, p);
         for (int p = 6; p < 6 + R; ++p)   // register bits stay where they are
-            if ((S >> from[p]) & 1) put(p, from[p]);
+            if ((S >> s.lay[p]) & 1) put(p, s.lay[p]);
         for (int p = 6; p < 6 + R; ++p)
             for (int b = 0; b < TB && to[p] < 0; ++b)
                 if (((S >> b) & 1) && !((placed >> b) & 1)) put(p, b);
         for (int p = 0; p < TB; ++p)
             for (int b = 0; b < TB && to[p] < 0; ++b)
                 if (!((placed >> b) & 1)) put(p, b);
-        TOp x{};
-        x.kind = TK_XCHG;
-        x.q0 = (int)s.lay.size() - 1;
-        x.lslot = -1;
-        s.items.push_back(x);
-        s.pre.push_back(std::move(s.pending));
-        s.pending.clear();
-        s.lay.push_back(to);
-        for (int p = 0; p < TB; ++p) s.at[to[p]] = p;
-        s.cost += dbl ? 36.0 : 18.0;
+        for (int p = 0; p < TB; ++p) {
+            s.lay[p] = to[p];
+            s.at[to[p]] = (int8_t)p;
+        }
+        s.cost += exchange_cost();
+        if (rec) {
+            rec->items.push_back({-1, (int)rec->lay.size() - 1, 0});
+            rec->pre.push_back(std::move(rec->pending));
+            rec->pending.clear();
+            rec->lay.push_back(std::vector<int>(s.lay, s.lay + TB));
+        }
     }
     bool storable(const State &s) const {
         for (int p = 0; p < hold; ++p)
             if (s.at[p] != p) return false;
         return true;
     }
-    void finish(State &s) {
-        if (!s.pending.empty() || !storable(s)) exchange(s, 0);
-        if (!found || s.cost < best.cost) {
-            best = std::move(s);
+    // the end of a pass: CNOTs that wait, or a layout it cannot store from, take an exchange
+    void finish(State &s, bool pending) {
+        if (pending || !storable(s)) exchange(s, 0);
+        if (!rec && (!found || s.cost < best_cost)) {
+            best = s.choice;
+            best_cost = s.cost;
             found = true;
         }
     }
-    void search(State s) {
+    // State t after one more choice: finished, or a candidate to go on from
+    void choose(Kind kind, uint32_t regs, State &&t, std::vector<State> &next) {
+        choices.push_back({kind, regs, t.choice});
+        t.choice = (int)choices.size() - 1;
+        if (kind == END) return finish(t, true);
+        emit(t, false);
+        if (t.left == 0) return finish(t, false);
+        if (found && t.cost >= best_cost) return;
+        for (const State &o : next)
+            if (o.left == t.left && o.cost <= t.cost && o.todo == t.todo && std::equal(t.lay, t.lay + TB, o.lay)) return;
+        next.push_back(std::move(t));
+    }
+    // weight: of the estimate of the exchanges to come
+    void search(State s, double weight) {
         emit(s, false);
-        if (s.left == 0) return finish(s);
-        if ((found && s.cost >= best.cost) || ++nodes > 2000) {
-            if (found) return;
-        }
-        for (int spare_low = 0; spare_low < 2; ++spare_low) {
-            State t = s;
-            absorb(t);
-            if (t.left == 0) {
-                finish(t);
-                break;
+        if (s.left == 0) return finish(s, false);
+        std::vector<State> beam, next;
+        beam.push_back(std::move(s));
+        auto guess = [&](const State &t) { return t.cost + weight * exchange_cost() * t.needs / R; };
+        while (!beam.empty()) {
+            next.clear();
+            for (State &t : beam) {
+                if (found && t.cost >= best_cost) continue;
+                State ready = t;   // without the CNOTs that the exchange performs
+                absorb(ready);
+                if (ready.left == 0) {
+                    choose(END, 0, std::move(ready), next);
+                } else {
+                    const uint32_t any = next_regs(ready, false), high = next_regs(ready, true);
+                    for (const uint32_t S : {any, high}) {
+                        if (S != any && S == 0) break;
+                        State u = ready;
+                        exchange(u, S);
+                        choose(EXCHANGE, S, std::move(u), next);
+                        if (high == any) break;
+                    }
+                }
+                const int left = t.left;   // what can run in this layout across lanes; interpreted: register CNOTs
+                emit(t, true);
+                if (t.left < left) choose(LANES, 0, std::move(t), next);
             }
-            const uint64_t S = next_regs(t, spare_low != 0);
-            if (spare_low && (S == 0 || S == next_regs(t, false))) break;
-            exchange(t, S);
-            search(std::move(t));
+            std::stable_sort(next.begin(), next.end(), [&](const State &x, const State &y) { return guess(x) < guess(y); });
+            if (next.size() > (size_t)kBeam) next.resize((size_t)kBeam);
+            beam.swap(next);
         }
-        State t = s;   // what can run in this layout across lanes; interpreted: register CNOTs
-        emit(t, true);
-        if (t.left < s.left) search(std::move(t));
+    }
+    Record run() {
+        State s;
+        s.todo.assign((ops.size() + 63) / 64, 0);
+        for (size_t k = 0; k < ops.size(); ++k) {
+            s.todo[k >> 6] |= 1ull << (k & 63);
+            s.needs += needs(k);
+        }
+        s.left = (int)ops.size();
+        for (int q = 0; q < TB; ++q) s.at[q] = s.lay[q] = (int8_t)q;
+        for (const double weight : {1.0, 0.3}) search(s, weight);
+        std::vector<Choice> path;
+        for (int k = best; k >= 0; k = choices[(size_t)k].before) path.push_back(choices[(size_t)k]);
+        Record out;
+        out.lay.push_back(std::vector<int>(s.lay, s.lay + TB));
+        rec = &out;
+        emit(s, false);
+        for (size_t k = path.size(); k-- > 0;) {
+            const Choice &c = path[k];
+            if (c.kind == LANES) {
+                emit(s, true);
+            } else {
+                absorb(s);
+                if (c.kind == EXCHANGE) exchange(s, c.regs);
+            }
+            emit(s, false);
+        }
+        finish(s, !out.pending.empty());
+        rec = nullptr;
+        return out;
     }
 };
 
 // The schedule of a pass: the execution order, the layouts, and per exchange
 // the index masks of every position before and after it.
 struct WidePlan {
-    WideScheduler::State best;
     int TB = 0;
+    std::vector<WideScheduler::Item> items;
+    std::vector<int> out;   // the layout the pass stores from
     std::vector<std::pair<std::vector<int>, std::vector<int>>> masks;   // old, new layout
 };
+// The schedules of a plan's passes by tile shape and operations (without
+// their matrices): passes that repeat are searched once.
+using WideMemo = std::unordered_map<std::string, WidePlan>;
 
 int gf2_rank(std::vector<int> v) {
     int r = 0;
@@ -1246,7 +1365,8 @@ int gf2_rank(std::vector<int> v) {
     return r;
 }
 
-WidePlan plan_wide(const dq_plan_s &p, const Step &S, bool lane_ops) {
+// A pass's operations as the scheduler takes them.
+std::vector<TOp> wide_ops(const dq_plan_s &p, const Step &S, bool lane_ops) {
     std::vector<TOp> ops;
     for (int64_t k = 0; k < S.nops; ++k) {
         const TOp &o = p.ops[(size_t)(S.op0 + k)];
@@ -1261,28 +1381,49 @@ WidePlan plan_wide(const dq_plan_s &p, const Step &S, bool lane_ops) {
             ops.push_back(c);
         }
     }
-    WideScheduler W{S.R, S.wb, 6 + S.R + S.wb, 3, p.mdbl, lane_ops, ops, {}, false, 0};
-    while (W.hold < 6 && S.lbits[W.hold - 3] == W.hold) ++W.hold;   // lanes that continue the low bits
-    W.hold = std::min(W.hold, 5);
-    WideScheduler::State s;
-    s.done.assign(ops.size(), 0);
-    s.left = (int)ops.size();
-    std::vector<int> id(W.TB);
-    for (int q = 0; q < W.TB; ++q) s.at[q] = id[q] = q;
-    s.lay.push_back(id);
-    W.search(s);
-    WidePlan out;
-    out.best = std::move(W.best);
+    return ops;
+}
+// and those operations in execution order at their positions, with the exchanges
+std::vector<TOp> wide_items(const std::vector<TOp> &ops, const WidePlan &W) {
+    std::vector<TOp> items;
+    for (const auto &it : W.items) {
+        TOp o{};
+        if (it.op >= 0) {
+            o = ops[(size_t)it.op];
+        } else {
+            o.kind = TK_XCHG;
+            o.lslot = -1;
+        }
+        o.q0 = it.q0;
+        o.q1 = it.q1;
+        items.push_back(o);
+    }
+    return items;
+}
+
+const WidePlan &plan_wide(const dq_plan_s &p, const Step &S, const std::vector<TOp> &ops, bool lane_ops, WideMemo &memo) {
+    int hold = 3;
+    while (hold < 6 && S.lbits[hold - 3] == hold) ++hold;   // lanes that continue the low bits
+    hold = std::min(hold, 5);
+    std::string key{(char)S.R, (char)S.wb, (char)hold, (char)lane_ops};
+    for (const TOp &o : ops) key += {(char)o.kind, (char)o.q0, (char)o.q1};
+    const auto hit = memo.emplace(std::move(key), WidePlan());
+    WidePlan &out = hit.first->second;
+    if (!hit.second) return out;
+    WideScheduler W(S.R, S.wb, hold, p.mdbl, lane_ops, ops);
+    WideScheduler::Record r = W.run();
     out.TB = W.TB;
-    for (size_t k = 0; k + 1 < out.best.lay.size(); ++k) {
+    out.items = std::move(r.items);
+    out.out = r.lay.back();
+    for (size_t k = 0; k + 1 < r.lay.size(); ++k) {
         // Index masks of the tile bits.  Reading in the new layout G: the
         // common lane bits and G's other lane bits are index bits 0..5; each
         // of the old layout's other lane bits is XORed onto one of the latter
         // beside an index bit of its own.  The old layout F writes where the
         // exchange's CNOTs move its elements: their columns are folded into
         // the masks, last CNOT first.
-        const std::vector<int> &F = out.best.lay[k], &G = out.best.lay[k + 1];
-        const auto &cnots = out.best.pre[k];
+        const std::vector<int> &F = r.lay[k], &G = r.lay[k + 1];
+        const auto &cnots = r.pre[k];
         std::vector<int> M(W.TB, 0), f, g;
         int lowb = 0, high = 6;
         for (int i = 0; i < 6; ++i) {
@@ -1337,10 +1478,12 @@ WidePlan plan_wide(const dq_plan_s &p, const Step &S, bool lane_ops) {
 // one-qubit diagonal gates one run, past gates on other bits.
 void wg_generate(dq_plan_s &p) {
     if (p.opt.jit) return;
+    WideMemo memo;
     auto gen = [&](Program &prog) {
         for (Step &S : prog.steps) {
             if (S.kind != ST_TILE || S.wb == 0) continue;
-            const WidePlan wp = plan_wide(p, S, false);
+            const std::vector<TOp> ops = wide_ops(p, S, false);
+            const WidePlan &wp = plan_wide(p, S, ops, false, memo);
             const int x0 = (int)p.wgx.size(), amp = sizeof(float);
             for (const auto &m : wp.masks) {
                 WgX X{};
@@ -1357,9 +1500,9 @@ void wg_generate(dq_plan_s &p) {
                 p.wgx.push_back(X);
             }
             auto phys = [&](int q) { return q < 3 ? q : (q < 6 ? S.lbits[q - 3] : (q < 6 + S.R ? S.rbits[q - 6] : S.wbits[q - 6 - S.R])); };
-            for (int q = 0; q < wp.TB; ++q) S.pout[q] = phys(wp.best.lay.back()[(size_t)q]);
+            for (int q = 0; q < wp.TB; ++q) S.pout[q] = phys(wp.out[(size_t)q]);
             S.wg0 = (int64_t)p.wgops.size();
-            const std::vector<TOp> &it = wp.best.items;
+            const std::vector<TOp> it = wide_items(ops, wp);
             std::vector<char> done(it.size(), 0);
             for (size_t i = 0; i < it.size(); ++i) {
                 if (done[i]) continue;
@@ -1423,11 +1566,11 @@ void wg_generate(dq_plan_s &p) {
     gen(p.adj);
 }
 
-WideSchedule wide_schedule(const dq_plan_s &p, const Step &S) {
-    const WidePlan W = plan_wide(p, S, true);
-    const WideScheduler::State &r = W.best;
+WideSchedule wide_schedule(const dq_plan_s &p, const Step &S, WideMemo &memo) {
+    const std::vector<TOp> ops = wide_ops(p, S, true);
+    const WidePlan &W = plan_wide(p, S, ops, true, memo);
     WideSchedule out;
-    out.items = r.items;
+    out.items = wide_items(ops, W);
     out.exchanges = (int)W.masks.size();
     auto list = [](const std::vector<int> &v) {
         std::string t;
@@ -1452,12 +1595,12 @@ WideSchedule wide_schedule(const dq_plan_s &p, const Step &S) {
                        "};\n    static constexpr int r[" + n + "] = {" + list(rd) + "};\n" + fold("wreg", "w") +
                        fold("rreg", "r") + low("wlow", w) + low("rlow", rd) + "};\n";
     }
-    out.layouts += "struct Out {\n    static constexpr int t[" + std::to_string(W.TB) + "] = {" + list(r.lay.back()) +
+    out.layouts += "struct Out {\n    static constexpr int t[" + std::to_string(W.TB) + "] = {" + list(W.out) +
                    "};\n    static constexpr int at(int p) { return t[p]; }\n};\n";
     return out;
 }
 
-std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) {
+std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0, WideMemo &memo) {
     s0 = -1;
     for (int64_t i = 0; i < S.nops; ++i) {
         const TOp &o = p.ops[(size_t)(S.op0 + i)];
@@ -1478,7 +1621,7 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
     // the operations at their positions: a workgroup tile's pass interleaves
     // them with exchanges of its layout
     WideSchedule sch;
-    if (S.wb) sch = wide_schedule(p, S);
+    if (S.wb) sch = wide_schedule(p, S, memo);
     else sch.items.assign(p.ops.begin() + S.op0, p.ops.begin() + S.op0 + S.nops);
     auto is_reg = [&](int q) { return q >= 6 && q < 6 + R; };
     if (S.wb) b += sch.layouts;
@@ -1598,6 +1741,7 @@ std::string pass_body(const dq_plan_s &p, const Step &S, bool adj, int64_t &s0) 
 
 void jit_generate(dq_plan_s &p) {
     std::map<std::string, int> index;
+    WideMemo memo;
     auto gen = [&](Program &prog, bool adj) {
         prog.jk.assign(prog.steps.size(), -1);
         prog.js0.assign(prog.steps.size(), 0);
@@ -1610,7 +1754,7 @@ void jit_generate(dq_plan_s &p) {
             // planner keeps them within the limit in any case)
             if (S.R < 6 && S.wb == 0 && S.nops * (int64_t(1) << S.R) > kJitMaxWork) continue;
             int64_t s0 = 0;
-            const std::string body = pass_body(p, S, adj, s0);
+            const std::string body = pass_body(p, S, adj, s0, memo);
             auto it = index.find(body);
             if (it == index.end()) {
                 const std::string name = jit_key(body);
