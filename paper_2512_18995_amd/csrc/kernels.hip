@@ -1476,51 +1476,58 @@ __global__ __launch_bounds__(256) void k_grad_final_multi(const char *ws, const 
 
 // ============================================================ launchers
 // ============================================================ measurement
-// Marginal probabilities in one linear read of the state.  The low LB bits
-// (512 complex64 or 256 complex128 amplitudes: 16 bytes a thread of a
-// 256-thread group) form a row of 4 KiB; the other bits are either measured
-// (block index y: with the row bits' outcome they name the marginal) or
-// walked row by row.  A thread therefore keeps one sum per amplitude of its
-// 16 bytes, whichever wires are measured, and every load is one contiguous
-// 4 KiB piece; the measured bits inside the row are sorted out once per
-// block: unmeasured lane bits by shuffles, the rest through LDS, in a fixed
-// order.  HBM-bound: ten wires of 27 qubits 436 -> 238 us (2.5 -> 4.5 TB/s;
-// before, each outcome's amplitudes were read apart, with ten zero bits
-// inserted into every index).
+// Marginal probabilities.  An index over the unmeasured bits is spread once
+// (zeros at the measured bits) and then advanced by masked additions: the
+// measured bits, set to ones, carry through.
+__device__ __forceinline__ uint64_t spread_step(uint64_t j, uint64_t step, uint64_t measured) {
+    return ((j | measured) + step) & ~measured;
+}
+
+// In one linear read of the state.  The low LB bits (512 complex64 or 256
+// complex128 amplitudes: 16 bytes a thread of a 256-thread group) form a row
+// of 4 KiB; the other bits are either measured (block index y: with the row
+// bits' outcome they name the marginal) or walked row by row by the block's G
+// groups.  A thread therefore keeps one sum per amplitude of its 16 bytes,
+// whichever wires are measured, and every load is one contiguous 4 KiB piece;
+// the measured bits inside the row are sorted out once per block: unmeasured
+// lane bits by shuffles, the rest through LDS, in a fixed order.  HBM-bound:
+// the ten middle wires of 27 qubits 186 us (5.8 TB/s; 225 by outcomes).
 template <typename T> constexpr int prob_lb() { return sizeof(T) == 4 ? 9 : 8; }
 
-template <typename T>
-__global__ __launch_bounds__(1024) void k_probs_part(const cx<T> *psi, ProbArgs a, int64_t rows, int64_t rpb,
-                                                     double *partial, int64_t bpo) {
+template <typename T, int G>
+__global__ __launch_bounds__(256 * G) void k_probs_rows(const cx<T> *psi, ProbArgs a, int64_t rows, int64_t rpb,
+                                                        double *partial, int64_t bpo) {
     constexpr int A = sizeof(T) == 4 ? 2 : 1, LB = prob_lb<T>(), U = 8;
     typedef T vld __attribute__((ext_vector_type(2 * A), aligned(2 * sizeof(T))));
-    __shared__ double sh[4][256 * A];
+    __shared__ double sh[G][256 * A];
     const int tid = threadIdx.x & 255;
     const int grp = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8));
     const int64_t oh = blockIdx.y, b = blockIdx.z;
-    uint64_t set = 0;
+    const int64_t r0 = (int64_t)blockIdx.x * rpb, r1 = r0 + rpb < rows ? r0 + rpb : rows;
+    uint64_t set = 0, measured = 0;   // rows' index bits above the row
+    int64_t j = r0 + grp, step = G;
     int out_hi = 0;
-    for (int i = 0; i < a.kh; ++i)
+    for (int i = 0; i < a.kh; ++i) {
+        const int at = a.hbit[i] - LB;
+        j = insert_zero(j, at);
+        step = insert_zero(step, at);
+        measured |= 1ull << at;
         if ((oh >> i) & 1) {
-            set |= 1ull << a.hbit[i];
+            set |= 1ull << at;
             out_hi |= 1 << a.hout[i];
         }
-    const cx<T> *p = psi + (b << a.n) + set + tid * A;
+    }
+    const cx<T> *p = psi + (b << a.n) + (set << LB) + tid * A;
     const bool active = (int64_t)tid * A < (int64_t(1) << a.n);   // registers shorter than a row
-    const int64_t r0 = (int64_t)blockIdx.x * rpb, r1 = r0 + rpb < rows ? r0 + rpb : rows;
     double acc[A] = {};
     if (active) {
-        for (int64_t r = r0 + grp; r < r1; r += 4 * U) {
+        for (int64_t r = r0 + grp; r < r1; r += G * U) {
             vld v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                int64_t j = r + 4 * u;
-                if (j >= r1) {
-                    v[u] = vld(T(0));
-                    continue;
-                }
-                for (int i = 0; i < a.kh; ++i) j = insert_zero(j, a.hbit[i] - LB);
-                v[u] = *(const vld *)(p + (j << LB));
+                v[u] = vld(T(0));
+                if (r + G * u < r1) v[u] = *(const vld *)(p + (j << LB));
+                j = spread_step(j, step, measured);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -1550,7 +1557,7 @@ __global__ __launch_bounds__(1024) void k_probs_part(const cx<T> *psi, ProbArgs 
     for (int e = 0; e < A; ++e) sh[grp][tid * A + e] = acc[e];
     __syncthreads();
     const int K = 1 << a.k;
-    for (int t = threadIdx.x; t < (1 << a.kl); t += blockDim.x) {
+    for (int t = threadIdx.x; t < (1 << a.kl); t += 256 * G) {
         int at = 0, o = out_hi;
         for (int i = 0; i < a.kl; ++i)
             if ((t >> i) & 1) {
@@ -1559,7 +1566,7 @@ __global__ __launch_bounds__(1024) void k_probs_part(const cx<T> *psi, ProbArgs 
             }
         // the row's bits that are wave bits of the group: 6 and 7 of tid
         double s = 0.0;
-        for (int g = 0; g < 4; ++g)
+        for (int g = 0; g < G; ++g)
             for (int w = 0; w < 4; ++w) {
                 const int wb = (w & 1) << (S + 6) | (w >> 1) << (S + 7);
                 if (wb & (int)low) continue;   // that bit is part of the outcome
@@ -1567,6 +1574,41 @@ __global__ __launch_bounds__(1024) void k_probs_part(const cx<T> *psi, ProbArgs 
             }
         partial[(b * K + o) * bpo + blockIdx.x] = s;
     }
+}
+
+// One outcome o (block index y) per block: chunk x of the values of the
+// unmeasured bits, one amplitude a thread and step (20 qubits, 16 samples, the
+// 10 highest bits: 68 us with every index spread anew, 38).
+template <typename T>
+__global__ __launch_bounds__(256) void k_probs_each(const cx<T> *psi, ProbArgs a, int64_t per_outcome, double *partial,
+                                                    int64_t bpo) {
+    __shared__ double red[4];
+    const int64_t o = blockIdx.y, b = blockIdx.z;
+    const int64_t r = (int64_t)blockIdx.x * PROB_CHUNK + threadIdx.x;
+    uint64_t set = 0, measured = 0;
+    int64_t j = r, step = 256;
+    auto measure = [&](int bit, int out) {   // bits ascending
+        j = insert_zero(j, bit);
+        step = insert_zero(step, bit);
+        measured |= 1ull << bit;
+        if ((o >> out) & 1) set |= 1ull << bit;
+    };
+    for (int i = 0; i < a.kl; ++i) measure(a.lbit[i], a.lout[i]);
+    for (int i = 0; i < a.kh; ++i) measure(a.hbit[i], a.hout[i]);
+    const cx<T> *p = psi + (b << a.n) + set;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int t = 0; t < (int)(PROB_CHUNK / 256); ++t) {
+        if (r + t * 256 < per_outcome) {
+            const cx<T> v = p[j];
+            acc += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+        }
+        j = spread_step(j, step, measured);
+    }
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) partial[((b << a.k) + o) * bpo + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // out[row] = sum of the row's bpo partials (row = b * 2^k + o), one wave, fixed order
@@ -1963,23 +2005,54 @@ hipError_t launch_hess_accum(const double *G, int64_t K, int64_t c0, int64_t mc,
     DQ_LAUNCH_RET;
 }
 
+// Which kernel, and how its blocks are cut (complex64 unless stated; times of
+// one call, most of it one launch).
+// - Measured bits all above the row and at most 32 rows an outcome: one outcome
+//   per block; its loads are contiguous, and a block of rows would pay its
+//   sorting for a few rows (20 qubits, 16 samples, the 10 highest bits: 38 us
+//   against 42 in rows; 22 qubits, 12: 12.9 against 14.4).
+// - Otherwise rows, by one group of 256 threads per block and about 2048 blocks
+//   (8192 if five or more bits above the row are measured: an outcome's rows
+//   then lie far apart, 27 qubits, 10 middle wires 215 -> 186 us).
+// - The workspace holds one partial sum per 4096 amplitudes of an outcome, so
+//   with many measured bits inside the row there are few blocks, each with many
+//   rows, about 42 ns apiece if four groups share them.  One outcome per block
+//   then reads each 64-byte piece once for every outcome in it, at 13 TB/s out
+//   of the L2 if the outcome's blocks follow each other, 6 with one block an
+//   outcome: the shorter of the two (the lowest 8 bits of 20, 22, 24, 26, 27
+//   qubits: 13, 27, 71, 318, 1320 us by outcomes, 85, 89, 90, 172, 203 by rows).
 hipError_t launch_probs(int dbl, const void *st, int64_t batch, const ProbArgs &a, double *partial, int64_t bpo,
                         double *out, hipStream_t s) {
     const int64_t rows = int64_t(1) << (a.n - a.kh > a.lb ? a.n - a.kh - a.lb : 0);
-    // at most bpo blocks per outcome (the workspace), about 2048 in all: with
-    // 1024 threads each that fills the chip twice over
-    int64_t rpb = (rows + bpo - 1) / bpo;
-    while (rpb < rows && ((rows / rpb) << a.kh) * batch > 2048) rpb *= 2;
-    bpo = (rows + rpb - 1) / rpb;
-    dim3 g((unsigned)bpo, 1u << a.kh, (unsigned)batch);
-    double *part = bpo == 1 ? out : partial;   // one block per outcome: nothing to add up
-    if (dbl)
-        hipLaunchKernelGGL(k_probs_part<double>, g, dim3(1024), 0, s, (const C128 *)st, a, rows, rpb, part, bpo);
-    else
-        hipLaunchKernelGGL(k_probs_part<float>, g, dim3(1024), 0, s, (const C64 *)st, a, rows, rpb, part, bpo);
+    const int64_t per_outcome = int64_t(1) << (a.n - a.k);
+    int64_t rpb = (rows + bpo - 1) / bpo;   // rows per block: at most bpo blocks (the workspace)
+    const int64_t cap = a.kh >= 5 ? 8192 : 2048;
+    while (rpb < rows && ((rows / rpb) << a.kh) * batch > cap) rpb *= 2;
+    const int64_t nrow = (rows + rpb - 1) / rpb;
+    int groups = 1;
+    bool each = a.kl == 0 && rows <= 32;
+    if (!each && (nrow << a.kh) * batch < 1024 && rpb >= 16) {
+        groups = 4;
+        const int64_t elem = dbl ? 16 : 8, run = a.kl ? elem << a.lbit[0] : 64;   // bytes, and of consecutive amplitudes
+        const double piece = (double)(elem * (run < 64 ? 64 / run : 1));
+        const double by_outcome = std::ldexp(piece * (double)batch, a.n) / (bpo > 1 ? 13e6 : 6e6);   // us
+        each = rpb >= 64 && by_outcome < 0.042 * (double)rpb;
+    }
+    const int64_t nb = each ? bpo : nrow;
+    const dim3 g((unsigned)nb, 1u << (each ? a.k : a.kh), (unsigned)batch);
+    double *part = nb == 1 ? out : partial;   // one block per outcome: nothing to add up
+    auto launch = [&](auto z) {
+        using T = decltype(z);
+        const cx<T> *psi = (const cx<T> *)st;
+        if (each) hipLaunchKernelGGL(k_probs_each<T>, g, dim3(256), 0, s, psi, a, per_outcome, part, nb);
+        else if (groups == 1) hipLaunchKernelGGL((k_probs_rows<T, 1>), g, dim3(256), 0, s, psi, a, rows, rpb, part, nb);
+        else hipLaunchKernelGGL((k_probs_rows<T, 4>), g, dim3(1024), 0, s, psi, a, rows, rpb, part, nb);
+    };
+    if (dbl) launch(double(0));
+    else launch(float(0));
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || bpo == 1) return e;
-    hipLaunchKernelGGL(k_probs_final, dim3((unsigned)(batch << a.k)), dim3(64), 0, s, (const double *)partial, bpo, out);
+    if (e != hipSuccess || nb == 1) return e;
+    hipLaunchKernelGGL(k_probs_final, dim3((unsigned)(batch << a.k)), dim3(64), 0, s, (const double *)partial, nb, out);
     DQ_LAUNCH_RET;
 }
 
