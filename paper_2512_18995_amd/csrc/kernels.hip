@@ -1622,7 +1622,32 @@ __global__ __launch_bounds__(64) void k_probs_final(const double *partial, int64
 
 // One shot per thread: the first outcome whose running sum exceeds u.  The
 // sums are the sequential float64 ones (they decide which outcome a uniform
-// near a boundary gives), so a block takes 256 shots of one distribution and
+// near a boundary gives).
+//
+// Each thread scanning its distribution: for few outcomes, or more
+// distributions than the sums below have blocks in flight.
+__global__ __launch_bounds__(256) void k_sample_scan(const double *p, int64_t batch, int nout, const double *u, int shots,
+                                                     int64_t *out) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= batch * shots) return;
+    const double *q = p + (i / shots) * nout;
+    const double x = u[i];
+    double c = 0.0;
+    int last = 0;   // the last outcome of nonzero probability so far
+    int64_t res = -1;
+    for (int m = 0; m < nout; ++m) {
+        const double pm = q[m];
+        if (pm > 0.0) last = m;
+        c += pm;
+        if (x < c) {
+            res = m;
+            break;
+        }
+    }
+    out[i] = res >= 0 ? res : last;
+}
+
+// With the sums formed once per block: a block takes 256 shots of one distribution and
 // forms them once, 2048 outcomes at a time in LDS, on one lane; each thread
 // then finds its outcome by bisection (entries that are negative or NaN make
 // the sums non-monotone: then by scanning them in order).  Bound by that
@@ -2056,10 +2081,24 @@ hipError_t launch_probs(int dbl, const void *st, int64_t batch, const ProbArgs &
     DQ_LAUNCH_RET;
 }
 
+// The estimates (us) are fits of both kernels' times over 2 to 4096 outcomes, 1
+// to 60000 distributions and 1 to 8192 shots.  A scan costs the latency of its
+// loads or, with many waves, their number; the sums the latency of one lane's
+// additions or, with many blocks, their number.  Up to 16 outcomes the scan is
+// never slower.  60000 distributions of 64 outcomes, one shot each: scan 11,
+// sums 282; 4096 shots of one distribution of 1024: 133 and 27.
 hipError_t launch_sample(const double *p, int64_t batch, int32_t nout, const double *u, int32_t shots, int64_t *out,
                          hipStream_t s) {
-    hipLaunchKernelGGL(k_sample, dim3((unsigned)((shots + 255u) / 256u), (unsigned)batch), dim3(256), 0, s, p, nout, u,
-                       shots, out);
+    const double per_dist = (double)((shots + 255u) / 256u), blocks = (double)batch * per_dist;
+    const double waves = (double)(batch * shots) / 64.0;
+    const double scan = std::max(2.0 + 0.145 * nout, waves * (1.5e-4 + 3.3e-5 * nout));
+    const double sums = std::max(3.0 + 0.027 * nout, blocks * (1.6e-3 + 3.0e-5 * nout));
+    if ((nout <= 16 || scan <= sums) && batch * shots < (int64_t(1) << 31)) {   // (one launch's threads)
+        hipLaunchKernelGGL(k_sample_scan, dim3((unsigned)((batch * shots + 255) / 256)), dim3(256), 0, s, p, batch, nout, u,
+                           shots, out);
+    } else {
+        hipLaunchKernelGGL(k_sample, dim3((unsigned)per_dist, (unsigned)batch), dim3(256), 0, s, p, nout, u, shots, out);
+    }
     DQ_LAUNCH_RET;
 }
 
