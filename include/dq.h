@@ -369,11 +369,15 @@ dq_status dq_profile_read(dq_plan plan, dq_profile *out, int32_t reset);
  * the 2^{n_c} amplitudes at packed offset state_off[c] of one state buffer,
  * its parameters the nparams_c doubles at param_off[c] of one parameter
  * buffer (dq_multi_layout fills both offset arrays; circuits are packed in
- * order, each state 256-byte aligned).  Register-tile passes of equal depth
- * of all circuits run as one kernel launch over every circuit's tiles, so a
- * step needs as many tile launches as the deepest circuit has passes, not
- * their sum; plans whose programs are not pure tile passes of the common
- * tile shape run through the single-plan path inside the same calls.  All
+ * order, each state 256-byte aligned).  Tile passes of equal depth of all
+ * circuits run as one kernel launch over every circuit's tiles, so a step
+ * needs about as many tile launches as the deepest circuit has passes, not
+ * their sum.  The first fused plan (arith64 = 0) sets the form of each
+ * direction, one-wave or workgroup tiles, and its register bits; plans that are
+ * pure tile passes of as many register bits join, and workgroup tiles of any
+ * size where the first plan's are such.  A plan of the other form, or compiled,
+ * is run as a plan of its circuit in the shared form that the multi-plan owns.
+ * The other plans run through the single-plan path inside the same calls.  All
  * per-circuit offsets are fixed at creation, so the launch sequence can be
  * captured in a HIP graph and replayed.  Data-encoded gates are not
  * supported here (ndata must be 0). */

@@ -3112,6 +3112,10 @@ struct dq_multi_s {
     int dbl = 0;
     int R_fwd = 0, R_adj = 0;
     std::vector<dq_plan> plans;
+    // the plan whose programs a circuit runs: the caller's, or one of the same
+    // circuit in the shared launches' form that the multi-plan owns
+    std::vector<dq_plan> run;
+    std::vector<std::unique_ptr<dq_plan_s>> own;
     std::vector<dq_obs> obs;
     std::vector<int64_t> st_off, par_off, out_off;
     int64_t st_total = 0, par_total = 0, out_total = 0;
@@ -3134,7 +3138,6 @@ struct dq_multi_s {
         int64_t first, count, units;
         int32_t max_nls;
     };
-    bool wg = false;
     std::vector<WgEntry> went;
     std::vector<std::pair<int, const Step *>> wref;
     std::vector<WgLaunch> wfwd, wadj;
@@ -3157,19 +3160,18 @@ struct dq_multi_s {
 
 namespace {
 
-bool tile_only(const Program &p, int R) {
-    for (const Step &s : p.steps)
-        if (s.kind != ST_TILE || s.R != R || s.wb != 0) return false;
-    return true;
-}
-bool wg_only(const Program &p) {
-    for (const Step &s : p.steps)
-        if (s.kind != ST_TILE || s.wb == 0) return false;
-    return true;
-}
-// interpreted workgroup tiles in both directions
-bool wg_plan(const dq_plan_s &p) {
-    return !p.opt.jit && p.wb_fwd > 0 && p.wb_adj > 0;
+// How a direction of a plan can join the shared launches: as one-wave tiles of
+// R register bits or as interpreted workgroup tiles of any shape.
+enum MultiForm { MF_NONE, MF_WAVE, MF_GROUP };
+const Program &multi_program(const dq_plan_s &p, int adj) { return adj ? p.adj : (p.has_fold ? p.fwd_fold : p.fwd_full); }
+int multi_bits(const dq_plan_s &p, int adj) { return adj ? p.R_adj : p.R_fwd; }
+MultiForm multi_form(const dq_plan_s &p, int adj) {
+    const int R = multi_bits(p, adj);
+    if (R <= 0 || p.opt.arith64) return MF_NONE;
+    for (const Step &s : multi_program(p, adj).steps)
+        if (s.kind != ST_TILE) return MF_NONE;
+    if ((adj ? p.wb_adj : p.wb_fwd) > 0) return p.opt.jit ? MF_NONE : MF_GROUP;
+    return (adj ? multi_adj_has(p.dbl, R) : multi_fwd_has(p.dbl, R)) ? MF_WAVE : MF_NONE;
 }
 
 MultiEntry make_entry(const Step &S, int n) {
@@ -3188,7 +3190,7 @@ MultiEntry make_entry(const Step &S, int n) {
 dq_status ensure_multi(dq_multi_s &m, dq_multi_s::Dev **out) {
     int dev = 0;
     DQ_HIP(hipGetDevice(&dev));
-    for (dq_plan p : m.plans) {
+    for (dq_plan p : m.run) {
         DevData *d = nullptr;
         dq_status st = ensure_device(*p, &d);
         if (st != DQ_OK) return st;
@@ -3204,7 +3206,7 @@ dq_status ensure_multi(dq_multi_s &m, dq_multi_s::Dev **out) {
     auto resolve = [&](const std::vector<MultiEntry> &v, const std::vector<int> &cs) {
         for (size_t i = 0; i < v.size(); ++i) {
             MultiEntry E = v[i];
-            DevData &d = m.plans[cs[i]]->dev[dev];
+            DevData &d = m.run[cs[i]]->dev[dev];
             E.ops = d.ops + (intptr_t)E.ops;
             E.lsg = d.lsg + (intptr_t)E.lsg;
             all.push_back(E);
@@ -3221,7 +3223,7 @@ dq_status ensure_multi(dq_multi_s &m, dq_multi_s::Dev **out) {
     std::vector<WgEntry> went(m.went);
     for (size_t i = 0; i < went.size(); ++i) {
         const int c = m.wref[i].first;
-        went[i].pass = make_wg_pass(*m.plans[c], m.plans[c]->dev[dev], *m.wref[i].second, went[i].pass.nt != 0);
+        went[i].pass = make_wg_pass(*m.run[c], m.run[c]->dev[dev], *m.wref[i].second, went[i].pass.nt != 0);
     }
     // the batched circuits' per-circuit steps, resolved for this device
     dq_multi_s::Dev D;
@@ -3230,7 +3232,7 @@ dq_status ensure_multi(dq_multi_s &m, dq_multi_s::Dev **out) {
     std::vector<MExp> ex;
     std::vector<MGrad> gr;
     for (int c : m.bc) {
-        dq_plan p = m.plans[c];
+        dq_plan p = m.run[c];
         DevData &d = p->dev[dev];
         const WsLayout &L = m.lay[c];
         const size_t wo = m.ws_off[c];
@@ -3339,17 +3341,55 @@ dq_status dq_multi_create(dq_multi *out, const dq_plan *plans, const dq_obs *obs
         m->plans.push_back(plans[c]);
         m->obs.push_back(obs[c]);
     }
-    // common tile shape: that of the first fused plan the shared kernels can run
+    // The first fused plan sets the form of each direction's shared launches
+    // and its register bits: one-wave tiles, or workgroup tiles, which batch
+    // whatever their size where its own are such.
+    const dq_plan_s *first = nullptr;
+    bool kernels = false, group[2] = {false, false};
     for (dq_plan p : m->plans)
         if (p->R_fwd > 0 && !p->opt.arith64) {
+            first = p;
             m->R_fwd = p->R_fwd;
             m->R_adj = p->R_adj;
-            m->wg = wg_plan(*p);
+            kernels = multi_fwd_has(m->dbl, m->R_fwd) && multi_adj_has(m->dbl, m->R_adj);   // of that size
+            for (int adj = 0; adj < 2; ++adj)
+                group[adj] = (adj ? p->wb_adj : p->wb_fwd) > 0 && !p->dbl && (!p->opt.jit || kernels);
             break;
         }
+    auto same_bits = [&](const dq_plan_s &p, int adj) { return kernels && multi_bits(p, adj) == (adj ? m->R_adj : m->R_fwd); };
+    auto joins = [&](const dq_plan_s &p) {
+        for (int adj = 0; adj < 2; ++adj)
+            if (multi_form(p, adj) != (group[adj] ? MF_GROUP : MF_WAVE) || !(group[adj] || same_bits(p, adj))) return false;
+        return true;
+    };
+    for (dq_plan p : m->plans) {
+        m->run.push_back(p);
+        if (joins(*p) || !first || p->opt.arith64) continue;
+        bool fits = true;
+        for (int adj = 0; adj < 2; ++adj)
+            fits = fits && multi_bits(*p, adj) > 0 &&
+                   (same_bits(*p, adj) || (group[adj] && multi_form(*p, adj) == MF_GROUP));
+        if (!fits) continue;
+        // tiles of the right size in the other form, or compiled for one
+        // circuit: the shared launches run a plan of the same circuit in
+        // theirs (launches of both forms at every depth would take longer: 16
+        // circuits of 12 to 15 qubits, every other one with five register bits
+        // given, 583 us against 345 in workgroup tiles)
+        std::unique_ptr<dq_plan_s> q(plan_clone_base(*p));
+        q->gates = p->canon;
+        q->one_wave = !group[0] && !group[1];
+        q->opt.jit = 0;
+        q->opt.tile_bits = first->opt.tile_bits;
+        q->opt.adj_tile_bits = first->opt.adj_tile_bits;
+        const dq_status st = complete_plan(q);
+        if (st != DQ_OK) return st;
+        if (!joins(*q)) continue;
+        m->run.back() = q.get();
+        m->own.push_back(std::move(q));
+    }
     const size_t amp = m->dbl ? 16 : 8;
     for (int c = 0; c < nplans; ++c) {
-        dq_plan p = m->plans[c];
+        dq_plan p = m->run[c];
         m->st_off.push_back(m->st_total);
         m->st_total += (int64_t)(align256(((size_t)1 << p->n) * amp) / amp);
         m->par_off.push_back(m->par_total);
@@ -3360,51 +3400,43 @@ dq_status dq_multi_create(dq_multi *out, const dq_plan *plans, const dq_obs *obs
         m->ws_off.push_back(m->ws_total);
         m->lay.push_back(L);
         m->ws_total += align256(L.total);
-        const Program &f = p->has_fold ? p->fwd_fold : p->fwd_full;
-        // batched: pure tile programs of the common shape, for which the
-        // multi-circuit kernels exist; the rest take the single-plan path
-        if (m->wg) {   // workgroup tiles batch whatever their register bits
-            m->batched.push_back(wg_plan(*p) && wg_only(f) && wg_only(p->adj));
-            continue;
-        }
-        m->batched.push_back(!p->opt.arith64 && p->R_fwd > 0 && p->R_fwd == m->R_fwd && p->R_adj == m->R_adj &&
-                             tile_only(f, m->R_fwd) &&
-                             tile_only(p->adj, m->R_adj) && multi_fwd_has(m->dbl, m->R_fwd) &&
-                             multi_adj_has(m->dbl, m->R_adj));
+        // batched: tile programs that fit the shared launches; the rest take
+        // the single-plan path
+        m->batched.push_back(joins(*p));
     }
     // adjoint waves per circuit: each wave walks tiles w, w + wps, ... and
     // leaves one row of partial gradient sums, which the final reduction
     // adds; capped, so that the rows stay few while the waves of all
     // circuits together still fill the device
     for (int c = 0; c < nplans; ++c) {
-        m->wps.push_back((int32_t)std::min<int64_t>(grad_waves(*m->plans[c], 1), kMultiWps));
+        m->wps.push_back((int32_t)std::min<int64_t>(grad_waves(*m->run[c], 1), kMultiWps));
         if (m->batched[c]) m->bc.push_back(c);
     }
     // depth tables
     const double tot_bytes = (double)m->st_total * (double)amp;   // all circuits' states
-    for (int pass = 0; pass < 2 && m->wg; ++pass) {
+    for (int pass = 0; pass < 2; ++pass) {   // workgroup tiles
         size_t depth = 0;
-        auto prog_of = [&](int c) -> const Program & {
-            const dq_plan_s &p = *m->plans[c];
-            return pass ? p.adj : (p.has_fold ? p.fwd_fold : p.fwd_full);
-        };
-        for (int c : m->bc) depth = std::max(depth, prog_of(c).steps.size());
+        std::vector<int> cs;
+        for (int c : m->bc)
+            if (multi_form(*m->run[c], pass) == MF_GROUP) cs.push_back(c);
+        for (int c : cs) depth = std::max(depth, multi_program(*m->run[c], pass).steps.size());
         for (size_t d = 0; d < depth; ++d)
             for (int R = MAX_TILE_R; R >= 1; --R) {
                 dq_multi_s::WgLaunch L{R, (int64_t)m->went.size(), 0, 0, 0};
-                for (int c : m->bc) {
-                    if (prog_of(c).steps.size() <= d || prog_of(c).steps[d].R != R) continue;
-                    const Step &S = prog_of(c).steps[d];
+                for (int c : cs) {
+                    const Program &prog = multi_program(*m->run[c], pass);
+                    if (prog.steps.size() <= d || prog.steps[d].R != R) continue;
+                    const Step &S = prog.steps[d];
                     WgEntry E{};
                     E.st_off = m->st_off[c];
                     E.mats_off = (int64_t)(m->ws_off[c] + m->lay[c].mats);
                     E.lam_off = (int64_t)(m->ws_off[c] + m->lay[c].lam);
                     E.part_off = (int64_t)(m->ws_off[c] + m->lay[c].part);
-                    E.ngrad = m->plans[c]->ngrad;
+                    E.ngrad = m->run[c]->ngrad;
                     E.wps = pass ? m->wps[c] : 1;
                     E.unit_begin = L.units;
                     E.pass.nt = tot_bytes * (pass ? 2 : 1) > kStreamBytes ? 1 : 0;
-                    L.units += pass ? E.wps : int64_t(1) << (m->plans[c]->n - 6 - S.R - S.wb);
+                    L.units += pass ? E.wps : int64_t(1) << (m->run[c]->n - 6 - S.R - S.wb);
                     L.max_nls = std::max<int32_t>(L.max_nls, (int32_t)S.nls);
                     ++L.count;
                     m->went.push_back(E);
@@ -3413,14 +3445,14 @@ dq_status dq_multi_create(dq_multi *out, const dq_plan *plans, const dq_obs *obs
                 if (L.count) (pass ? m->wadj : m->wfwd).push_back(L);
             }
     }
-    for (int pass = 0; pass < 2 && !m->wg; ++pass) {
+    for (int pass = 0; pass < 2; ++pass) {   // one-wave tiles
         auto &tab = pass ? m->adj : m->fwd;
         auto &tabc = pass ? m->adj_c : m->fwd_c;
         auto &units = pass ? m->adj_units : m->fwd_units;
-        for (int c = 0; c < nplans; ++c) {
-            if (!m->batched[c]) continue;
-            dq_plan p = m->plans[c];
-            const Program &prog = pass ? p->adj : (p->has_fold ? p->fwd_fold : p->fwd_full);
+        for (int c : m->bc) {
+            dq_plan p = m->run[c];
+            if (multi_form(*p, pass) != MF_WAVE) continue;
+            const Program &prog = multi_program(*p, pass);
             for (size_t d = 0; d < prog.steps.size(); ++d) {
                 if (tab.size() <= d) {
                     tab.resize(d + 1);
@@ -3460,6 +3492,7 @@ void dq_multi_destroy(dq_multi m) try {
             (void)hipSetDevice(cur);
         }
     }
+    for (auto &q : m->own) dq_plan_destroy(q.release());
     delete m;
 } DQ_CATCH_VOID
 

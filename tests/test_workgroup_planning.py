@@ -27,3 +27,45 @@ def test_planning_time_stays_that_of_one_wave_tiles(jit):
         wide = _seconds(lambda: dq.Plan(c, "c64", jit=jit))
         narrow = _seconds(lambda: dq.Plan(c, "c64", jit=jit, tile_bits=5, adj_tile_bits=4))
         assert wide < 6 * narrow + 0.005, (c.n, wide, narrow)
+
+
+def _batched(dtype, specs):
+    plans, obs = [], []
+    for n, opt in specs:
+        w = W.config(5, n=n, layers=2)
+        plans.append(dq.Plan(w.circuit, dtype, **opt))
+        obs.append(dq.Observable(n, w.observables))
+    return dq.Multi(plans, obs).batched
+
+
+@pytest.mark.parametrize("adj", [3, 4])
+@pytest.mark.parametrize("n", [10, 11, 12, 16])
+def test_workgroup_forward_beside_a_one_wave_adjoint_is_batched(n, adj):
+    """adj_tile_bits keeps the adjoint in one-wave tiles and leaves the forward its workgroup tiles: each direction
+    joins the shared launches in its own form."""
+    d = dq.Plan(W.config(5, n=n, layers=2).circuit, "c64", adj_tile_bits=adj).describe().splitlines()
+    assert all(("wbits=" in l) == l.startswith("fwd") for l in d if " tile " in l)
+    assert _batched("c64", [(n, {"adj_tile_bits": adj})] * 4) == [True] * 4
+
+
+@pytest.mark.parametrize("dtype,specs", [
+    ("c64", [(12, {"tile_bits": 5}), (12, {}), (14, {}), (13, {"tile_bits": 5})]),
+    ("c64", [(12, {}), (13, {"tile_bits": 5}), (10, {})]),
+    ("c64", [(10, {}), (11, {"tile_bits": 4})]),
+    ("c64", [(10, {"jit": True}), (10, {"jit": True}), (10, {})]),
+    ("c64", [(10, {"jit": True, "adj_tile_bits": 3}), (10, {"adj_tile_bits": 3})]),
+    ("c64", [(12, {"adj_tile_bits": 4}), (13, {"tile_bits": 5}), (14, {})]),
+    ("c128", [(10, {"jit": True, "adj_tile_bits": 3}), (11, {})])])
+def test_tile_forms_of_one_size_are_batched_together(dtype, specs):
+    """One-wave and workgroup tiles of as many register bits, compiled plans of ten qubits included (the shared
+    launches interpret them)."""
+    assert all(_batched(dtype, specs))
+
+
+def test_other_sizes_take_the_single_plan_path():
+    """The first fused plan sets the size: other one-wave sizes, compiled workgroup tiles of other registers, dense
+    blocks and float64 arithmetic stay alone."""
+    assert _batched("c64", [(12, {"dense_fuse": 4}), (12, {}), (13, {})]) == [False, True, True]
+    assert _batched("c64", [(12, {"tile_bits": 5}), (12, {"tile_bits": 4}), (13, {})]) == [True, False, True]
+    assert _batched("c64", [(12, {"jit": True}), (10, {"jit": True})]) == [False, False]
+    assert _batched("c64", [(10, {}), (10, {"jit": True, "arith64": True}), (10, {"jit": True})]) == [True, False, True]
