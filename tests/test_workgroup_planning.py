@@ -69,3 +69,15 @@ def test_other_sizes_take_the_single_plan_path():
     assert _batched("c64", [(12, {"tile_bits": 5}), (12, {"tile_bits": 4}), (13, {})]) == [True, False, True]
     assert _batched("c64", [(12, {"jit": True}), (10, {"jit": True})]) == [False, False]
     assert _batched("c64", [(10, {}), (10, {"jit": True, "arith64": True}), (10, {"jit": True})]) == [True, False, True]
+
+
+@pytest.mark.parametrize("dtype,jit", [("c64", False), ("c64", True), ("c128", True), ("c128", False)])
+@pytest.mark.parametrize("n", [8, 10, 20, 31, 32])
+def test_candidates_hold_the_default_plan(dtype, jit, n):
+    """The tuners can return the plan that a caller gets without options (workgroup tiles from 10 to 31 qubits)."""
+    c = W.config(5, n=n, layers=1).circuit
+    default = dq.Plan(c, dtype, jit=jit).describe()
+    assert any(dq.Plan(c, dtype, tile_bits=o["tile_bits"], dense_fuse=o["dense_fuse"], jit=o["jit"]).describe() == default
+               for o in dq.candidate_options(dtype, n, jit))
+    if not jit:
+        assert n < 9 or any(dq.Plan(c, dtype, **o).describe() == default for o in dq.multi_candidates(dtype))
