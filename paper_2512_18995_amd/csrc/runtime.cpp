@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -1904,8 +1905,9 @@ dq_status complete_plan(std::unique_ptr<dq_plan_s> &p) {
         else wg_generate(*p);
         if (!p->opt.jit || !p->wb_fwd || p->n > 17 || p->n <= 6 + p->Rt_fwd + p->wb_fwd) return DQ_OK;
         const Program &f = p->has_fold ? p->fwd_fold : p->fwd_full;
-        std::vector<int> kernels(f.jk);
-        kernels.insert(kernels.end(), p->adj.jk.begin(), p->adj.jk.end());
+        std::vector<int> kernels;   // (-1: a step that is no compiled pass)
+        for (const Program *prog : {&f, (const Program *)&p->adj})
+            std::copy_if(prog->jk.begin(), prog->jk.end(), std::back_inserter(kernels), [](int k) { return k >= 0; });
         std::sort(kernels.begin(), kernels.end());
         if (std::unique(kernels.begin(), kernels.end()) != kernels.end()) return DQ_OK;
         std::unique_ptr<dq_plan_s> q(plan_clone_base(*p));

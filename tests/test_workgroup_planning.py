@@ -81,3 +81,17 @@ def test_candidates_hold_the_default_plan(dtype, jit, n):
                for o in dq.candidate_options(dtype, n, jit))
     if not jit:
         assert n < 9 or any(dq.Plan(c, dtype, **o).describe() == default for o in dq.multi_candidates(dtype))
+
+
+@pytest.mark.parametrize("unitaries", [0, 1, 3])
+def test_steps_without_a_kernel_do_not_share_one(unitaries):
+    """Compiled plans of 15 to 17 qubits keep workgroup tiles if two passes share a kernel: sweeps of dense unitaries,
+    which have none, do not count as two that do."""
+    rng = np.random.default_rng(23)
+    c = W.random_circuit(rng, 16, 60, [o for o in W.ALL_OPS if o != "unitary"])
+    for k in range(unitaries):
+        c.gates.insert(20 * (k + 1), W.Gate("unitary", (k, k + 5, k + 9), matrix=W.random_unitary(rng, 3)))
+    steps = [l for l in dq.Plan(c, "c64", jit=True).describe().splitlines() if " tile " in l or " sweep " in l]
+    kernels = [l.split(" kernel=")[1].split()[0] for l in steps if " kernel=" in l]
+    assert len(kernels) == len(set(kernels)) < len(steps) + (unitaries == 0)
+    assert not any("wbits=" in l for l in steps)
