@@ -98,7 +98,7 @@ struct WgX {               // LDS byte masks per position of the old and new lay
 };
 struct WgPass {
     int32_t n, R, nops, nls, nt;
-    int32_t touch;                           // read the two-qubit diagonal gates' matrices ahead
+    int32_t diags;                           // 1: two-qubit diagonal gates among the operations
     int32_t pin[WG_MAX_T], pout[WG_MAX_T];   // physical bit of every position, on load and on store
     int32_t tbits[WG_MAX_T];                 // the tile's physical bits above 2, ascending
     const WgOp *ops;

@@ -150,7 +150,7 @@ struct Step {
     int32_t wbits[MAX_TILE_W] = {0};
     int32_t tbits[MAX_TILE_R + 3 + MAX_TILE_W] = {0};
     int64_t wg0 = 0, nwg = 0;       // interpreted workgroup tile: into plan.wgops
-    int32_t wgtouch = 0;                       // 1: eight or more two-qubit diagonal gates
+    int32_t wgdiags = 0;            // 1: two-qubit diagonal gates among them
     int32_t pout[WG_MAX_T] = {0};   // and its physical bit of every position on store
     int64_t op0 = 0, nops = 0;      // into plan.ops
     int64_t ls0 = 0, nls = 0;       // into plan.lsg
@@ -1559,7 +1559,7 @@ void wg_generate(dq_plan_s &p) {
             }
             S.nwg = (int64_t)p.wgops.size() - S.wg0;
             const auto from = p.wgops.begin() + S.wg0;
-            S.wgtouch = std::count_if(from, p.wgops.end(), [](const WgOp &w) { return w.kind == WG_2QDIAG; }) >= 8;
+            S.wgdiags = std::any_of(from, p.wgops.end(), [](const WgOp &w) { return w.kind == WG_2QDIAG; });
         }
     };
     gen(p.fwd_full);
@@ -2162,7 +2162,7 @@ WgPass make_wg_pass(const dq_plan_s &p, const DevData &d, const Step &S, bool nt
     a.nops = (int32_t)S.nwg;
     a.nls = (int32_t)S.nls;
     a.nt = nt ? 1 : 0;
-    a.touch = S.wgtouch;
+    a.diags = S.wgdiags;
     for (int q = 0; q < 6 + S.R + S.wb; ++q) {
         a.pin[q] = q < 3 ? q : (q < 6 ? S.lbits[q - 3] : (q < 6 + S.R ? S.rbits[q - 6] : S.wbits[q - 6 - S.R]));
         a.pout[q] = S.pout[q];

@@ -16,8 +16,10 @@
 // 128, and 300 per tile outside its gates.  Two workgroups fit a compute unit
 // (64 KiB of exchange buffer and 16 KiB of gradient sums in an adjoint pass).
 // Gradient step, one-wave passes -> these: 64 circuits of 12 to 22 qubits
-// 26.1 -> 18.0 ms (the vector units issue 95 % of the time in both), 12
-// qubits and 64 samples 368 -> 291 us.
+// 26.1 -> 18.0 ms, 12 qubits and 64 samples 368 -> 291 and, with the heads of
+// the entries in lanes (WgHeads), 276 us; two layers of CZ or RZZ gates between
+// each wire and the next six, 16 qubits, forward 116 and 167 us in one-wave
+// passes, 140 and 204 without those heads, 127 and 181 with them.
 #include "dq_internal.h"
 
 #include <type_traits>
@@ -28,8 +30,58 @@ namespace {
 
 constexpr int WB = WG_WAVE_BITS;
 
+__device__ __forceinline__ int rl(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
 // one uniform field of a table in the constant address space
 __device__ __forceinline__ int fld(cptr<WgOp> o, int k) { return o->a[k]; }
+// The first words of the operations, lane l holding those of operation l of
+// its group of 64, and in passes with two-qubit diagonal gates (diags) their
+// matrices' diagonals: read by scalar loads, an entry and then its matrix are
+// two dependent misses of the scalar cache, which nothing hides when few
+// workgroups run.
+struct WgHead {
+    int kind, a0, a1, a2;
+};
+struct WgHeads {
+    WgHead mine;
+    float d[8];
+    int group = -1;
+    __device__ __forceinline__ WgHead of(const WgOp *ops, int nops, int k, const cx<float> *mats, bool diags, int lane) {
+        if ((k >> 6) != group) {
+            group = k >> 6;
+            const int l = (group << 6) + lane;
+            const WgOp *o = ops + (l < nops ? l : nops - 1);
+            mine = WgHead{o->kind, o->a[0], o->a[1], o->a[2]};
+            if (diags) {
+                const cx<float> *m = mats + (mine.kind == WG_2QDIAG ? mine.a2 : 0);
+                const int step = mine.kind == WG_2QDIAG ? 5 : 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const cx<float> e = m[i * step];
+                    d[2 * i] = e.x;
+                    d[2 * i + 1] = e.y;
+                }
+            }
+        }
+        const int l = k & 63;
+        return WgHead{rl(mine.kind, l), rl(mine.a0, l), rl(mine.a1, l), rl(mine.a2, l)};
+    }
+    __device__ __forceinline__ cx<float> diag(int k, int i) const {
+        return cx<float>{__int_as_float(rl(__float_as_int(d[2 * i]), k & 63)), __int_as_float(rl(__float_as_int(d[2 * i + 1]), k & 63))};
+    }
+};
+// static choice by a uniform index: binary, a chain of comparisons costs up to ten
+template <int LO, int HI, typename F> __device__ __forceinline__ void pick(int i, F &&f) {
+    if constexpr (HI - LO == 1) {
+        f(std::integral_constant<int, LO>{});
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (i < MID) pick<LO, MID>(i, f);
+        else pick<MID, HI>(i, f);
+    }
+}
+// register bits (a, b), a < b, of pair b (b - 1) / 2 + a
+constexpr int pair_hi(int p) { int b = 1; while (b * (b + 1) / 2 <= p) ++b; return b; }
+constexpr int pair_lo(int p) { return p - pair_hi(p) * (pair_hi(p) - 1) / 2; }
 
 __device__ __forceinline__ int64_t wg_base(int64_t t, int T, const int32_t *tb) {
     int64_t base = t << 3;
@@ -100,10 +152,11 @@ __device__ __forceinline__ void wg_xchg(cx<T> (&v)[NS][1 << R], char *buf, const
 // taken; left to itself the compiler writes results to fresh registers and
 // copies the whole tile back at the joins (64 moves beside the 128 multiply-
 // adds of a gate on two states).  Results that overwrite an operand avoid it.
-//   a = m a + t (m uniform), the same with m per lane, and a = m a
+//   a = m a + t (m uniform), the same with m per lane
 __device__ __forceinline__ void fma_in(float &a, float m, float t) { asm("v_fma_f32 %0, %1, %0, %2" : "+v"(a) : "s"(m), "v"(t)); }
 __device__ __forceinline__ void fma_lane(float &a, float m, float t) { asm("v_fma_f32 %0, %1, %0, %2" : "+v"(a) : "v"(m), "v"(t)); }
-__device__ __forceinline__ void mul_in(float &a, float m) { asm("v_mul_f32 %0, %1, %0" : "+v"(a) : "v"(m)); }
+// flips the signs of the lanes whose mask is the sign bit (else 0)
+__device__ __forceinline__ void flip_in(float &a, int mask) { asm("v_xor_b32 %0, %1, %0" : "+v"(a) : "v"(mask)); }
 __device__ __forceinline__ void swap_in(float &a, float &b) { asm volatile("v_swap_b32 %0, %1" : "+v"(a), "+v"(b)); }
 
 // the register forms of tile_dev.h (same operations, same rounding), in place
@@ -158,7 +211,6 @@ template <typename T> __device__ __forceinline__ void mul_lane(cx<T> &a, cx<T> f
 // exactly 1 (of a uniform value: scalar compares)
 __device__ __forceinline__ bool is_one(cx<float> f) { return __float_as_int(f.x) == 0x3f800000 && (__float_as_int(f.y) << 1) == 0; }
 
-__device__ __forceinline__ int rl(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
 __device__ __forceinline__ double rl_f64(float x, int l) { return (double)__int_as_float(rl(__float_as_int(x), l)); }
 
 // A run of one-qubit diagonal gates at any positions as one product diagonal:
@@ -221,15 +273,17 @@ __device__ __forceinline__ void wg_diag(cx<T> (&v)[NS][1 << R], std::integer_seq
 
 template <typename T, int NS, int R>
 __device__ __forceinline__ void wg_ops(cx<T> (&v)[NS][1 << R], cptr<WgOp> ops, int nops, const WgDiag *diag,
-                                       const WgX *xs, const cx<T> *mats, char *buf, double *acc, int pos, int lane,
+                                       const WgX *xs, const cx<T> *mats, bool diags, char *buf, double *acc, int pos, int lane,
                                        int wave) {
     using V = cx<T>;
     constexpr int NR = 1 << R;
     const cptr<V> m = to_const(mats);
     auto isreg = [](int q) { return q >= 6 && q < 6 + R; };
+    WgHeads heads;
     for (int k = 0; k < nops; ++k) {
         const cptr<WgOp> o = ops + k;
-        switch (o->kind) {
+        const WgHead h = heads.of((const WgOp *)ops, nops, k, mats, diags, lane);
+        switch (h.kind) {
         case WG_REAL: {   // one real 2x2 (RY, H, X, Z) on each register bit of the block
             T c[R > 0 ? R : 1][4];
 #pragma unroll
@@ -280,13 +334,13 @@ __device__ __forceinline__ void wg_ops(cx<T> (&v)[NS][1 << R], cptr<WgOp> ops, i
             });
             break;
         case WG_DIAG:
-            wg_diag<T, NS, R>(v, std::make_integer_sequence<int, R>{}, diag + fld(o, 0), fld(o, 1), fld(o, 2) != 0, mats,
+            wg_diag<T, NS, R>(v, std::make_integer_sequence<int, R>{}, diag + h.a0, h.a1, h.a2 != 0, mats,
                               pos, lane, wave, acc);
             break;
         case WG_CNOT: {   // control a[0] anywhere, target register a[1]
             // swaps under the control's branch: in the lanes whose lane or
             // wave bit is set, or of the register pairs whose bit is set
-            const int qc = fld(o, 0), kt = fld(o, 1);
+            const int qc = h.a0, kt = h.a1;
             const bool rc = isreg(qc), lc = (pos >> qc) & 1;
             static_for<0, R>([&](auto bc) {
                 constexpr int b = decltype(bc)::value;
@@ -319,100 +373,133 @@ __device__ __forceinline__ void wg_ops(cx<T> (&v)[NS][1 << R], cptr<WgOp> ops, i
             break;
         }
         case WG_CZ: {     // any positions
-            const int q0 = fld(o, 0), q1 = fld(o, 1);
-            const bool r0 = isreg(q0), r1 = isreg(q1);
-            DQ_SF(NR, {
-                const int b0 = r0 ? (i >> (q0 - 6)) & 1 : (pos >> q0) & 1;
-                const int b1 = r1 ? (i >> (q1 - 6)) & 1 : (pos >> q1) & 1;
-                const T sg = (b0 & b1) ? T(-1) : T(1);
-                DQ_NS({
-                    mul_in(v[s_][i].x, sg);
-                    mul_in(v[s_][i].y, sg);
+            // only the amplitudes with both register bits set change (with every
+            // amplitude multiplied by its sign, found register by register, 25
+            // qubits and two layers of 25 controlled rotations took 2230 us
+            // forward, against 1838 in one-wave passes and 1808 now)
+            const int q0 = h.a0, q1 = h.a1;
+            const bool r0 = isreg(q0), r1 = isreg(q1), p0 = (pos >> q0) & 1, p1 = (pos >> q1) & 1;
+            constexpr int SIGN = (int)0x80000000;
+            if (!r0 && !r1) {
+                const int flip = p0 && p1 ? SIGN : 0;
+                DQ_SF(NR, {
+                    DQ_NS({
+                        flip_in(v[s_][i].x, flip);
+                        flip_in(v[s_][i].y, flip);
+                    });
                 });
-            });
+            } else if (r0 != r1) {
+                const int flip = (r0 ? p1 : p0) ? SIGN : 0, kr = (r0 ? q0 : q1) - 6;
+                pick<0, R>(kr, [&](auto kc) {
+                    constexpr int k = decltype(kc)::value;
+                    DQ_SF(NR, {
+                        if constexpr ((i >> k) & 1) {
+                            DQ_NS({
+                                flip_in(v[s_][i].x, flip);
+                                flip_in(v[s_][i].y, flip);
+                            });
+                        }
+                    });
+                });
+            } else {
+                const int lo = (q0 < q1 ? q0 : q1) - 6, hi = (q0 < q1 ? q1 : q0) - 6;
+                pick<0, R *(R - 1) / 2>(hi * (hi - 1) / 2 + lo, [&](auto pc) {
+                    constexpr int a = pair_lo(decltype(pc)::value), b = pair_hi(decltype(pc)::value);
+                    DQ_SF(NR, {
+                        if constexpr (((i >> a) & 1) && ((i >> b) & 1)) {
+                            DQ_NS({
+                                flip_in(v[s_][i].x, SIGN);
+                                flip_in(v[s_][i].y, SIGN);
+                            });
+                        }
+                    });
+                });
+            }
             break;
         }
         case WG_2QDIAG: { // diag over (a[0] = msb, a[1]); slot a[2], generator a[3], gradient slot a[4]
-            const int q0 = fld(o, 0), q1 = fld(o, 1), sl = fld(o, 2);
+            const int q0 = h.a0, q1 = h.a1;
             const bool r0 = isreg(q0), r1 = isreg(q1);
             const bool p0 = (pos >> q0) & 1, p1 = (pos >> q1) & 1;
-            if constexpr (NS == 2) {
-                const int ls = fld(o, 4);
-                if (ls >= 0) {
-                    T s = 0;
-                    const bool zz = fld(o, 3) == GEN_ZZ;
-                    DQ_SF(NR, {
-                        const T t = im_dot<T>(v[1][i], v[0][i]);
-                        const bool b0 = r0 ? ((i >> (q0 - 6)) & 1) != 0 : p0, b1 = r1 ? ((i >> (q1 - 6)) & 1) != 0 : p1;
-                        s += zz ? ((b0 != b1) ? -t : t) : ((b0 && b1) ? t : T(0));
-                    });
-                    wide_acc<WB>(acc, ls, lane, wave, (double)s);
-                }
-            }
-            const V d0 = ldc(m, sl), d1 = ldc(m, sl + 5), d2 = ldc(m, sl + 10), d3 = ldc(m, sl + 15);
+            const int ls = NS == 2 ? fld(o, 4) : -1;
+            const bool zz = fld(o, 3) == GEN_ZZ;   // else |11><11|
+            auto term = [&](T s) {
+                if constexpr (NS == 2) wide_acc<WB>(acc, ls, lane, wave, (double)s);
+            };
+            const V d0 = heads.diag(k, 0), d1 = heads.diag(k, 1), d2 = heads.diag(k, 2), d3 = heads.diag(k, 3);
             // the factors by the values of the register bits among the two
             // (a lane or wave bit's value is this lane's)
             // a controlled phase: only the amplitudes with both bits set change
             const bool cp = is_one(d0) && is_one(d1) && is_one(d2);
             const V f00 = csel(!r0 && p0, csel(!r1 && p1, d3, d2), csel(!r1 && p1, d1, d0));
             if (!r0 && !r1) {
+                if constexpr (NS == 2)
+                    if (ls >= 0) {
+                        const T s = all_sum<T, V, NR>(v[0], v[1]);
+                        term(zz ? (p0 != p1 ? -s : s) : (p0 && p1 ? s : T(0)));
+                    }
                 if (!cp || (p0 && p1)) DQ_SF(NR, { DQ_NS({ mul_lane(v[s_][i], f00); }); });
             } else if (r0 != r1) {
                 const V f1 = r0 ? csel(p1, d3, d2) : csel(p0, d3, d1);
                 const int kr = (r0 ? q0 : q1) - 6;
-                static_for<0, R>([&](auto kc) {
+                const bool p = r0 ? p1 : p0;
+                pick<0, R>(kr, [&](auto kc) {
                     constexpr int k = decltype(kc)::value;
-                    if (kr == k) {
-                        if (!cp) {
-                            DQ_SF(NR, {
-                                if constexpr (!((i >> k) & 1)) { DQ_NS({ mul_lane(v[s_][i], f00); }); }
-                            });
+                    if constexpr (NS == 2)
+                        if (ls >= 0) {
+                            if (zz) {
+                                const T s = reg_z_sum<T, V, NR, k>(v[0], v[1]);
+                                term(p ? -s : s);
+                            } else {
+                                const T s = reg_set_sum<T, V, NR, k>(v[0], v[1]);
+                                term(p ? s : T(0));
+                            }
                         }
-                        if (!cp || (r0 ? p1 : p0)) {
-                            DQ_SF(NR, {
-                                if constexpr ((i >> k) & 1) { DQ_NS({ mul_lane(v[s_][i], f1); }); }
-                            });
-                        }
+                    if (!cp) {
+                        DQ_SF(NR, {
+                            if constexpr (!((i >> k) & 1)) { DQ_NS({ mul_lane(v[s_][i], f00); }); }
+                        });
+                    }
+                    if (!cp || p) {
+                        DQ_SF(NR, {
+                            if constexpr ((i >> k) & 1) { DQ_NS({ mul_lane(v[s_][i], f1); }); }
+                        });
                     }
                 });
             } else {
                 const int lo = (q0 < q1 ? q0 : q1) - 6, hi = (q0 < q1 ? q1 : q0) - 6;
                 const V flo = q0 < q1 ? d2 : d1, fhi = q0 < q1 ? d1 : d2;   // only the lower, only the higher bit set
-                static_for<0, R>([&](auto ac) {
-                    static_for<0, R>([&](auto bc) {
-                        constexpr int a = decltype(ac)::value, b = decltype(bc)::value;
-                        if constexpr (a < b)
-                            if (lo == a && hi == b) {
-                                DQ_SF(NR, {
-                                    constexpr int x = ((i >> a) & 1) + 2 * ((i >> b) & 1);
-                                    if constexpr (x == 3) { DQ_NS({ mul_lane(v[s_][i], d3); }); }
-                                });
-                                if (!cp) {
-                                    DQ_SF(NR, {
-                                        constexpr int x = ((i >> a) & 1) + 2 * ((i >> b) & 1);
-                                        const V f = x == 0 ? d0 : x == 1 ? flo : fhi;
-                                        if constexpr (x != 3) { DQ_NS({ mul_lane(v[s_][i], f); }); }
-                                    });
-                                }
-                            }
+                pick<0, R *(R - 1) / 2>(hi * (hi - 1) / 2 + lo, [&](auto pc) {
+                    constexpr int a = pair_lo(decltype(pc)::value), b = pair_hi(decltype(pc)::value);
+                    if constexpr (NS == 2)
+                        if (ls >= 0) {
+                            if (zz) term(reg_zz_sum<T, V, NR, a, b>(v[0], v[1]));
+                            else term(reg_p11_sum<T, V, NR, a, b>(v[0], v[1]));
+                        }
+                    DQ_SF(NR, {
+                        constexpr int x = ((i >> a) & 1) + 2 * ((i >> b) & 1);
+                        if constexpr (x == 3) { DQ_NS({ mul_lane(v[s_][i], d3); }); }
                     });
+                    if (!cp) {
+                        DQ_SF(NR, {
+                            constexpr int x = ((i >> a) & 1) + 2 * ((i >> b) & 1);
+                            const V f = x == 0 ? d0 : x == 1 ? flo : fhi;
+                            if constexpr (x != 3) { DQ_NS({ mul_lane(v[s_][i], f); }); }
+                        });
+                    }
                 });
             }
             break;
         }
-        case WG_XCHG: wg_xchg<T, NS, R>(v, buf, xs + fld(o, 0), wave, lane); break;
+        case WG_XCHG:
+            wg_xchg<T, NS, R>(v, buf, xs + h.a0, wave, lane);
+            break;
         default: break;
         }
     }
 }
 
-// One pass over the tiles t0, t0 + step, ... < t1 of one sample.  A two-
-// qubit diagonal gate is two dependent scalar loads, entry and matrix, that
-// nothing hides when few workgroups run; in passes of many of them (a.touch)
-// each thread first reads one gate's lines, all at once behind the loads of
-// the state, which brings them into this die's L2 (the Fourier transform of
-// 14, 18 and 22 qubits: 146, 234, 478 -> 130, 203, 425 us).  Passes of blocks
-// and runs have few entries and lose 2 to 5 % by it.
+// One pass over the tiles t0, t0 + step, ... < t1 of one sample.
 template <typename T, int NS, int R>
 __device__ __forceinline__ void wg_tiles(const WgPass &a, cx<T> *st, cx<T> *lam, const cx<T> *mats, int64_t t0,
                                          int64_t t1, int64_t step, char *buf, double *acc) {
@@ -424,8 +511,6 @@ __device__ __forceinline__ void wg_tiles(const WgPass &a, cx<T> *st, cx<T> *lam,
     const int64_t li = wg_lane_off(lane, a.pin), lo = wg_lane_off(lane, a.pout);
     const int64_t wi = wg_wave_off<R>(wave, a.pin), wo = wg_wave_off<R>(wave, a.pout);
     cx<T> *const base_of[2] = {st, lam};
-    int gate = -1;
-    if (a.touch && (int)threadIdx.x < a.nops && a.ops[threadIdx.x].kind == WG_2QDIAG) gate = a.ops[threadIdx.x].a[2];
     for (int64_t t = t0; t < t1; t += step) {
         int64_t base = wg_base(t, 6 + R + WB, a.tbits);
         V v[NS][NR];
@@ -437,11 +522,7 @@ __device__ __forceinline__ void wg_tiles(const WgPass &a, cx<T> *st, cx<T> *lam,
                 DQ_SF(NR, { v[s_][i] = (p + wg_reg_off<R>(i, a.pin))[li]; });
             }
         });
-        if (a.touch && t == t0 && gate >= 0) {
-            const V x = mats[gate], y = mats[gate + 15];
-            asm volatile("" ::"v"(x.x), "v"(y.x));
-        }
-        wg_ops<T, NS, R>(v, to_const(a.ops), a.nops, a.diag, a.xs, mats, buf, acc, pos, lane, wave);
+        wg_ops<T, NS, R>(v, to_const(a.ops), a.nops, a.diag, a.xs, mats, a.diags != 0, buf, acc, pos, lane, wave);
         asm volatile("" : "+s"(base));
         DQ_NS({
             V *p = base_of[s_] + base + wo;
