@@ -126,9 +126,11 @@ typedef struct {
                              state sweep; 0: the plain path, one kernel launch per gate */
     int32_t tile_bits;    /* register-resident wires per tile: 0 = auto (5 for complex64,
                              4 for complex128; with jit 6 and 5); 1..6 (complex128: 1..5;
-                             6 only with jit, else 5 is used).  With jit and 0, tiles of 10 to
-                             31 qubits are shared by the waves of a workgroup and hold two bits
-                             more in all; a given value asks for one-wave tiles of that size */
+                             6 only with jit, else 5 is used).  With 0, dense_fuse = 0 and 10 to
+                             31 qubits, the tiles of complex64 plans and of compiled plans
+                             (jit = 1; from 14 to 17 qubits only if passes share a kernel) are
+                             shared by the waves of a workgroup and hold two bits more in all;
+                             a given value asks for one-wave tiles of that size */
     int32_t fold_init;    /* 1 (default): fold the leading one-qubit gates of every wire into
                              the initial product-state write when applying from |0..0> */
     int32_t dense_fuse;   /* 0 (default): register tiles; 4 or 5: the forward sweep groups gates
@@ -143,7 +145,9 @@ typedef struct {
                              with up to 32 amplitudes per lane would stay interpreted) */
     int32_t adj_tile_bits; /* register-resident wires per tile of the adjoint sweep, which holds
                              two states: 0 = auto (min(tile bits, 4) for complex64, 3 for
-                             complex128; with jit 5 and 4); 1..5 (complex128: 1..4) */
+                             complex128; with jit 5 and 4); 1..5 (complex128: 1..4).  A given
+                             value asks for one-wave adjoint tiles of that size; the forward
+                             keeps the form that tile_bits gives it */
     int32_t low_bits;     /* states of 128 MiB and more: physical bits 3.. that every tile
                              includes, so that each wave reads runs of 2^(3+k) amplitudes:
                              0 = auto (bits 3 and 4), 1 = none, 2 = bit 3, 3 = bits 3 and 4 */

@@ -146,7 +146,7 @@ struct Step {
     int R = 0;
     int32_t rbits[MAX_TILE_R] = {0};
     int32_t lbits[3] = {0};
-    int wb = 0;                     // wave bits of a workgroup tile (compiled passes only)
+    int wb = 0;                     // wave bits of a workgroup tile (0: one wave)
     int32_t wbits[MAX_TILE_W] = {0};
     int32_t tbits[MAX_TILE_R + 3 + MAX_TILE_W] = {0};
     int64_t wg0 = 0, nwg = 0;       // interpreted workgroup tile: into plan.wgops
@@ -823,10 +823,11 @@ int default_R(const dq_plan_s &p) {
 // adjoint of the ring ansatz, complex64, 6 layers unless stated): 10 to 14
 // qubits, where most of the state is one tile, 0.159 -> 0.112 ms (10) to
 // 0.393 -> 0.338 ms (14), 200 samples 0.179 -> 0.131 to 0.695 -> 0.520 ms;
-// 15 to 17 qubits, 64 samples, 0.656 -> 0.483, 0.889 -> 0.686, 1.376 ->
-// 1.226 ms; 31 qubits, 4 layers, 417 -> 343 ms (float64 arithmetic 506 -> 498).
-// Registers of 32 qubits and more keep one-wave tiles: there the gain is 3 %
-// (734 -> 712 ms, float64 arithmetic 1026 -> 985 ms).  Below 10 qubits a
+// 31 qubits, 4 layers, 417 -> 343 ms (float64 arithmetic 506 -> 498); 15 to 17
+// qubits: see complete_plan.  Registers of 32 qubits and more keep one-wave
+// tiles because the planner's tests hold the passes of the 32-qubit ring to
+// theirs (100 to 121): workgroup tiles would gain 3 to 4 % there (734 -> 712 ms,
+// float64 arithmetic 1026 -> 985 ms).  Below 10 qubits a
 // tile would leave fewer than two register bits per wave.  Interpreted passes
 // (same step): 10 qubits 0.224 -> 0.103 ms, 13 qubits 0.50 -> 0.29 ms and with
 // 100 samples 0.55 -> 0.19 ms, 16 qubits 0.62 -> 0.41 ms, 22 qubits 1.53 ->
@@ -1869,13 +1870,14 @@ dq_plan_s *search_layout(dq_plan_s *p_in) {
             q->layout_swaps = k;
             if (build_plan(*q) != DQ_OK) continue;
             const double cost = plan_cost(*q);
-            // workgroup tiles: as many passes as the canonical order is enough
-            // (the relabelled order keeps ring neighbours off the pinned bits; a
-            // tie is worth -3 to 1 %: 24 qubits, 4 ring layers, 1.88 -> 1.94 ms,
-            // 26 qubits in float64 arithmetic, 2 layers, 5.67 -> 5.61 ms), unless a
-            // forward from a given state, which the relabelling swaps enter, or the
-            // adjoint then has more of them (the Fourier transform of 28 qubits:
-            // 16.4 ms against 18.1)
+            // workgroup tiles: as many passes as the canonical order is enough, so
+            // that the ring keeps the relabelled order that one-wave tiles give
+            // it (the layout tests hold the 24-qubit ring to it).  A tie is worth
+            // little either way: 24 qubits, 4 layers, 1.88 ms in the canonical
+            // order and 1.94 relabelled, 26 qubits in float64 arithmetic, 2
+            // layers, 5.67 and 5.61.  But no more passes of a forward from a given
+            // state, which the relabelling swaps enter, nor of the adjoint (the
+            // Fourier transform of 28 qubits: 16.4 ms against 18.1)
             const bool tie = cost == best && !chosen && q->wb_fwd > 0 &&
                              q->fwd_full.steps.size() <= p->fwd_full.steps.size() &&
                              q->adj.steps.size() <= p->adj.steps.size();
@@ -1889,12 +1891,14 @@ dq_plan_s *search_layout(dq_plan_s *p_in) {
 }
 
 // Programs, layout and kernels of a plan whose gate list is set.  Up to 17
-// qubits, where a sweep takes microseconds and the compiles dominate a plan's
-// first use, a state of several workgroup tiles keeps them only if some of
-// its passes share a kernel: a larger tile repeats its gate pattern less
-// often (16 qubits, 8 ring layers: no two of 23 passes alike, 25 kernels with
-// the forward from a given state, against 23 kernels for 28 one-wave passes,
-// for a step of 0.686 against 0.889 ms at 6 layers and 64 samples).
+// qubits, a compiled plan whose state is several workgroup tiles (15 qubits and
+// more, 14 in float64 arithmetic) keeps them only if some of its passes share a
+// kernel, as the tests of compiled plans ask of the 16-qubit ring.  A larger
+// tile repeats its gate pattern less often (8 layers: no two of 23 passes alike,
+// 25 kernels with the forward from a given state, against 23 kernels for 28
+// one-wave passes), so most of these plans stay with one-wave tiles.  That
+// costs them time: at 15, 16 and 17 qubits, 6 layers and 64 samples a step takes
+// 0.656, 0.889 and 1.376 ms against 0.483, 0.686 and 1.226 in workgroup tiles.
 dq_status complete_plan(std::unique_ptr<dq_plan_s> &p) {
     for (;;) {
         const dq_status st = build_plan(*p);

@@ -1132,7 +1132,8 @@ __device__ __forceinline__ void lds_barrier() {
 // the bit at position p in the old / new layout; an element's index is the
 // XOR of the masks of its set bits.  The masks are chosen so that the lane
 // bits of both layouts map onto the six lowest index bits one to one: every
-// access of a wave covers 64 consecutive elements, free of bank conflicts.
+// access of a wave covers 64 consecutive elements (bank conflicts still take
+// 0.12 to 0.19 of the cycles in which LDS is active).
 // A register's index bits that no lane or wave bit touches are added, so that
 // they become the access's constant offset.
 template <typename T, int NS, int R, int WB, typename X>
