@@ -3171,11 +3171,14 @@ namespace {
 enum MultiForm { MF_NONE, MF_WAVE, MF_GROUP };
 const Program &multi_program(const dq_plan_s &p, int adj) { return adj ? p.adj : (p.has_fold ? p.fwd_fold : p.fwd_full); }
 int multi_bits(const dq_plan_s &p, int adj) { return adj ? p.R_adj : p.R_fwd; }
+bool multi_tiles(const dq_plan_s &p, int adj) {   // pure tile passes
+    const auto &steps = multi_program(p, adj).steps;
+    return multi_bits(p, adj) > 0 && !p.opt.arith64 &&
+           std::all_of(steps.begin(), steps.end(), [](const Step &s) { return s.kind == ST_TILE; });
+}
 MultiForm multi_form(const dq_plan_s &p, int adj) {
     const int R = multi_bits(p, adj);
-    if (R <= 0 || p.opt.arith64) return MF_NONE;
-    for (const Step &s : multi_program(p, adj).steps)
-        if (s.kind != ST_TILE) return MF_NONE;
+    if (!multi_tiles(p, adj)) return MF_NONE;
     if ((adj ? p.wb_adj : p.wb_fwd) > 0) return p.opt.jit ? MF_NONE : MF_GROUP;
     return (adj ? multi_adj_has(p.dbl, R) : multi_fwd_has(p.dbl, R)) ? MF_WAVE : MF_NONE;
 }
@@ -3370,10 +3373,10 @@ dq_status dq_multi_create(dq_multi *out, const dq_plan *plans, const dq_obs *obs
     };
     for (dq_plan p : m->plans) {
         m->run.push_back(p);
-        if (joins(*p) || !first || p->opt.arith64) continue;
+        if (joins(*p) || !first) continue;
         bool fits = true;
         for (int adj = 0; adj < 2; ++adj)
-            fits = fits && multi_bits(*p, adj) > 0 &&
+            fits = fits && multi_tiles(*p, adj) &&
                    (same_bits(*p, adj) || (group[adj] && multi_form(*p, adj) == MF_GROUP));
         if (!fits) continue;
         // tiles of the right size in the other form, or compiled for one

@@ -95,3 +95,13 @@ def test_steps_without_a_kernel_do_not_share_one(unitaries):
     kernels = [l.split(" kernel=")[1].split()[0] for l in steps if " kernel=" in l]
     assert len(kernels) == len(set(kernels)) < len(steps) + (unitaries == 0)
     assert not any("wbits=" in l for l in steps)
+
+
+def test_a_multi_plan_makes_no_second_plan_of_a_circuit_that_cannot_join():
+    """A dense unitary is a sweep of its own in every form: such circuits keep the caller's plan alone."""
+    c = W.random_circuit(np.random.default_rng(3), 10, 400, [o for o in W.ALL_OPS if o != "unitary"])
+    u = W.Circuit(10, c.gates + [W.Gate("unitary", (1, 4, 7), matrix=W.random_unitary(np.random.default_rng(1), 3))], c.n_params)
+    obs = [dq.Observable(10, [W.tfim_open(10)])] * 2
+    plans = [dq.Plan(c, "c64"), dq.Plan(u, "c64")]
+    assert dq.Multi(plans, obs).batched == [True, False]
+    assert _seconds(lambda: dq.Multi(plans, obs)) < 0.5 * _seconds(lambda: dq.Plan(u, "c64"))
